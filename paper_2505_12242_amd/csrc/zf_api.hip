@@ -603,7 +603,7 @@ zf_status zf_colnorm(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
     e = zf::launch_cm_colnorm(single_table(), d, colnorm_grid(d), as_stream(stream));
   else
     e = zf::launch_colnorm(single_table(), d, colnorm_grid(d), single_table(),
-                           ceil_div(m, zf::kFinalizeCols), static_cast<double*>(ws),
+                           ceil_div(m, zf::kFinCols), static_cast<double*>(ws),
                            as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -1015,7 +1015,7 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
       // separate pass reuses the column-score workspace (cn_rb x m doubles)
       if (cm) zs_doubles += d.m * static_cast<int64_t>(d.cm_nch) * zf::kCmWaves;
       off_zen[q] = p->blk_zen;
-      p->blk_zen += ceil_div(d.m, zf::kZenCols);
+      p->blk_zen += ceil_div(d.m, cm ? zf::kZenCols : zf::kFinCols);
       off_zp[q] = p->blk_zp;
       if (!cm) p->blk_zp += ceil_div(d.m, zf::kZenCols) * static_cast<int64_t>(d.cn_rb);
     }
@@ -1029,7 +1029,7 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
     off_sel[q] = p->blk_sel;
     off_unp[q] = p->blk_unp;
     p->blk_cn += colnorm_grid(d);
-    p->blk_fin += cm ? 0 : ceil_div(d.m, zf::kFinalizeCols);
+    p->blk_fin += cm ? 0 : ceil_div(d.m, zf::kFinCols);
     p->blk_top += 1;
     p->blk_up += update_grid(d);
     if (d.rv) p->blk_upv += rv_grid(d);

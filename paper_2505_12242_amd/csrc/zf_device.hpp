@@ -167,6 +167,37 @@ __device__ __forceinline__ void buf_put_b64(u32x2 v, rsrc_t r, uint32_t voff, ui
   __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, AUX);
 }
 
+// Second stage of the row-major column sums: column j's cn_rb row-block
+// partials (rows of m doubles at p) added in a fixed order -- wave w of the
+// block the w-th contiguous share of them, in row-block order, then the waves'
+// sums in wave order through `red`.  Every thread of the block calls it; the
+// result is valid in the first kFinCols threads.
+__device__ __forceinline__ double finalize_sum(const double* __restrict__ p, int32_t rb, int64_t m,
+                                               int64_t j, double (&red)[kFinSegs][kFinCols]) {
+  constexpr int kBatch = 8;  // loads in flight per lane
+  const int lane = threadIdx.x & 63;
+  const int wave = uniform_i32(threadIdx.x >> 6);
+  const int32_t per = (rb + kFinSegs - 1) / kFinSegs;
+  const int32_t r1 = min(rb, (wave + 1) * per);
+  double s = 0.0;
+  if (j < m) {
+    for (int32_t r = wave * per; r < r1; r += kBatch) {
+      double v[kBatch];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b)
+        v[b] = r + b < r1 ? p[static_cast<int64_t>(r + b) * m + j] : 0.0;
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) s += v[b];
+    }
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  s = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < kFinSegs; ++w) s += red[w][lane];
+  return s;
+}
+
 // One Adam/AdamW element update; each line is one fp32 operation (the
 // library is compiled without contraction, with correctly rounded sqrt and
 // division).

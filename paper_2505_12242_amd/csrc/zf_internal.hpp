@@ -16,7 +16,9 @@ namespace zf {
 constexpr int kThreads = 256;
 constexpr int kColnormCols = 512;
 constexpr int kUpdateCols = 256;
-constexpr int kFinalizeCols = 256;
+constexpr int kFinCols = 64;  // row-major column sums, second stage: columns per block
+constexpr int kFinSegs = 8;   // and waves, each adding a share of their partials
+constexpr int kFinThreads = kFinCols * kFinSegs;
 constexpr int kTopkThreads = 1024;
 
 // Row-major update with 16-byte accesses: a block covers rv_w <= kRvMaxCols
@@ -47,7 +49,9 @@ constexpr int kCmSelChunk = kThreads * 4;  // rows per block of the selected-onl
 constexpr int kCmColnormCols = kThreads / 64;
 constexpr int kCmWaves = kThreads / 64;  // waves per update block (one statistics partial each)
 
-// Zen-auto: channels per finalize block; threads of the one-block total.
+// Zen-auto: channels per finalize block (channel-major; row-major kFinCols)
+// and columns per block of the row-major statistics pass; threads of the
+// one-block total.
 constexpr int kZenCols = 256;
 constexpr int kZenTotalThreads = 256;
 

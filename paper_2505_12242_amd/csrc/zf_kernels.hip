@@ -17,8 +17,8 @@ namespace {
 // cn_rpb-row tile in fp64 (squares of bf16 values are exact), each lane
 // owning 8 adjacent columns and reading them with one 16-byte load per row;
 // the four waves take interleaved rows and are combined in LDS in fixed
-// order.  Stage 2 adds the row-block partials of each column in order and
-// rounds once to fp32.  No atomics: the result is deterministic.
+// order.  Stage 2 adds the row-block partials of each column in a fixed order
+// and rounds once to fp32.  No atomics: the result is deterministic.
 // ---------------------------------------------------------------------------
 
 constexpr int kCnBatch = 4;  // rows per wave loaded before they are added
@@ -119,17 +119,22 @@ __global__ __launch_bounds__(kThreads) void colnorm_partial_kernel(const DevMat*
   }
 }
 
+// Stage 2 is a chain of dependent fp64 additions behind loads that are m
+// doubles apart, so what bounds it is latency: one thread per column walking
+// its cn_rb partials took 62.7 us for a 4096 x 4096 weight (256 partials a
+// column, 16 blocks on the chip), seven times the pass over G itself.  Here
+// the kFinSegs waves of a block take a contiguous share of the partials of 64
+// columns each, 8 loads in flight (finalize_sum): 4.3 us, and 5.8 us against 27.9 us for the layer of
+// seven Llama-2-7B weights (16 to 43 partials a column).
 template <bool BATCHED>
-__global__ __launch_bounds__(kFinalizeCols) void colnorm_finalize_kernel(
+__global__ __launch_bounds__(kFinThreads) void colnorm_finalize_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one, const double* __restrict__ ws) {
   int64_t local;
-  const DevMat d = get_mat<BATCHED>(mats, off, nmats, one, local);
-  const int64_t j = local * kFinalizeCols + threadIdx.x;
-  if (j >= d.m) return;
-  double s = 0.0;
-  const double* p = ws + d.cn_ws + j;
-  for (int32_t r = 0; r < d.cn_rb; ++r) s += p[static_cast<int64_t>(r) * d.m];
-  d.norms[j] = static_cast<float>(s);
+  const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
+  const int64_t j = local * kFinCols + (threadIdx.x & 63);
+  __shared__ double red[kFinSegs][kFinCols];
+  const double s = finalize_sum(ws + d.cn_ws, d.cn_rb, d.m, j, red);
+  if (threadIdx.x < kFinCols && j < d.m) d.norms[j] = static_cast<float>(s);
 }
 
 // ---------------------------------------------------------------------------
@@ -797,7 +802,7 @@ hipError_t launch_colnorm(const Table& t, const DevMat& one, int64_t blocks, con
   }
   if (fin_blocks > 0)
     ZF_LAUNCH(colnorm_finalize_kernel, dim3(static_cast<uint32_t>(fin_blocks)),
-              dim3(kFinalizeCols), s, tf, one, static_cast<const double*>(ws));
+              dim3(kFinThreads), s, tf, one, static_cast<const double*>(ws));
   return hipGetLastError();
 }
 

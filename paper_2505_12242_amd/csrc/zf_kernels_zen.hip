@@ -108,19 +108,22 @@ __global__ __launch_bounds__(kZenCols) void rm_zen_partial_kernel(const DevMat* 
   zs[d.cn_ws + rblk * d.m + c] = s;
 }
 
+// The partials are added as in the column scores' second stage; the block's
+// 64 square roots then in a fixed butterfly (8.4 us for the seven weights of a
+// Llama-2-7B layer, 39.0 us with one thread per column: latency, see there).
 template <bool BATCHED>
-__global__ __launch_bounds__(kZenCols) void rm_zen_finalize_kernel(
+__global__ __launch_bounds__(kFinThreads) void rm_zen_finalize_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one,
     const double* __restrict__ zs, double* __restrict__ zb) {
   int64_t local;
   const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
-  const int tid = threadIdx.x;
-  const int64_t c = local * kZenCols + tid;
+  const int64_t c = local * kFinCols + (threadIdx.x & 63);
+  __shared__ double red[kFinSegs][kFinCols];
+  const double s = finalize_sum(zs + d.cn_ws, d.cn_rb, d.m, c, red);
+  if (threadIdx.x >= kFinCols) return;
   double root_sel = 0.0, root_acc = 0.0;
   if (c < d.m) {
-    double s = 0.0;
-    for (int32_t rb = 0; rb < d.cn_rb; ++rb) s += zs[d.cn_ws + static_cast<int64_t>(rb) * d.m + c];
     const float f = static_cast<float>(s);
     const double root = sqrt(static_cast<double>(f));
     if (c < d.k) {
@@ -131,21 +134,14 @@ __global__ __launch_bounds__(kZenCols) void rm_zen_finalize_kernel(
       root_acc = root;
     }
   }
-  __shared__ double red[2][kZenCols];
-  red[0][tid] = root_sel;
-  red[1][tid] = root_acc;
-  __syncthreads();
 #pragma unroll
-  for (int h = kZenCols / 2; h >= 1; h >>= 1) {
-    if (tid < h) {
-      red[0][tid] += red[0][tid + h];
-      red[1][tid] += red[1][tid + h];
-    }
-    __syncthreads();
+  for (int o = 32; o >= 1; o >>= 1) {
+    root_sel += __shfl_xor(root_sel, o, 64);
+    root_acc += __shfl_xor(root_acc, o, 64);
   }
-  if (tid == 0) {
-    zb[2 * b] = red[0][0];
-    zb[2 * b + 1] = red[1][0];
+  if (threadIdx.x == 0) {
+    zb[2 * b] = root_sel;
+    zb[2 * b + 1] = root_acc;
   }
 }
 
@@ -223,7 +219,7 @@ hipError_t launch_rm_zen(const Table& tp, int64_t partial_blocks, const Table& t
                        dim3(kZenCols), 0, s, tp.mats, tp.off, tp.nmats, one, zs);
   if (finalize_blocks > 0)
     hipLaunchKernelGGL((rm_zen_finalize_kernel<true>),
-                       dim3(static_cast<uint32_t>(finalize_blocks)), dim3(kZenCols), 0, s, tf.mats,
+                       dim3(static_cast<uint32_t>(finalize_blocks)), dim3(kFinThreads), 0, s, tf.mats,
                        tf.off, tf.nmats, one, zs, zb);
   return hipGetLastError();
 }
