@@ -140,10 +140,27 @@ __global__ __launch_bounds__(kFinThreads) void colnorm_finalize_kernel(
 // ---------------------------------------------------------------------------
 // a2: selection.  One 1024-thread block per matrix.  Scores are mapped to
 // unsigned keys that order like the float values (with -0.0 == +0.0); an
-// MSB-first 8-bit radix select finds the k-th largest key T and how many
-// keys equal to T are taken; a compaction pass in ascending column order
-// then emits sel / unsel, the 64-bit mask words (one wave ballot each) and
-// their prefix counts.  Among keys equal to T the lowest columns win.
+// MSB-first radix select over digits of 11, 11 and 10 bits finds the k-th
+// largest key T and how many keys equal to T are taken; a pass in ascending
+// column order then emits sel / unsel, the 64-bit mask words (one wave ballot
+// each) and their prefix counts.  Among keys equal to T the lowest columns win.
+//
+// One block on one CU, where 64 lanes execute one instruction a cycle: what
+// bounds it is latency (loads, barriers) for a few thousand columns and the
+// instructions spent per column beyond, not the 12 bytes a column.  So
+//   - each wave owns one contiguous range of mask words and, up to
+//     64 * 16 * kTopkMaxWords columns, keeps its keys in registers: the scores
+//     are read once, all loads in flight;
+//   - the first digit holds two mantissa bits besides the exponent, so scores
+//     of a few binades spread over many LDS counters, and the later digits
+//     touch the few keys that share the digits before; a digit whose keys are
+//     all taken ends the search (two digits nearly always);
+//   - the output pass needs one barrier: the waves count what they hold first
+//     and then write their ranges independently.
+// Measured (10% selected, one launch): 512 columns 5.8 -> 3.8 us, 4096 11.5 ->
+// 5.4, 11008 28.4 -> 12.5, 28672 61.1 -> 21.1, against four 8-bit digits that
+// read the scores again each time and an output pass with four barriers per
+// 1024 columns.
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ uint32_t order_key(float x) {
@@ -152,48 +169,96 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Block-wide exclusive count of `flag` over the 16 waves of a topk block.
-// Returns the count before this thread; *total receives the block total,
-// *wave_before the count of the waves before this one, *ballot the wave's
-// ballot.  Contains two barriers.
-__device__ __forceinline__ uint32_t block_excl_count(bool flag, uint32_t* sh_wave,
-                                                     uint32_t* total, uint32_t* wave_before,
-                                                     uint64_t* ballot) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const uint64_t b = __ballot(flag);
-  if (lane == 0) sh_wave[wave] = static_cast<uint32_t>(__popcll(b));
-  __syncthreads();
-  uint32_t before = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kTopkThreads / 64; ++w) {
-    const uint32_t c = sh_wave[w];
-    before += (w < wave) ? c : 0u;
-    tot += c;
-  }
-  __syncthreads();
-  *total = tot;
-  *wave_before = before;
-  *ballot = b;
-  return before + lanes_below(b);
+constexpr int kTopkWaves = kTopkThreads / 64;
+constexpr int kTopkBins = 2048;
+constexpr int kTopkMaxWords = 32;  // words a wave holds in registers
+static_assert(kTopkBins == 2 * kTopkThreads && kTopkWaves == 16, "two bins a thread, one row of waves");
+
+struct TopkShared {
+  uint32_t hist[3][kTopkBins];
+  uint32_t wave_a[kTopkWaves], wave_b[kTopkWaves];
+  uint32_t digit, above, here;
+};
+
+// Inclusive sum over the lanes of the wave up to this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
 }
 
-template <bool BATCHED>
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one) {
-  int64_t local;
-  const DevMat d = get_mat<BATCHED>(mats, off, nmats, one, local);
-  const int64_t m = d.m;
-  const int64_t k = d.k;
-  if (m == 0) return;
+// Sum of v[0 .. wave - 1] (v: one value per wave, in LDS).
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* v, int lane, int wave) {
+  const uint32_t incl = wave_scan(lane < kTopkWaves ? v[lane] : 0u);
+  return wave > 0 ? __builtin_amdgcn_readlane(incl, wave - 1) : 0u;
+}
+
+// After a digit's counts are complete: the digit in which the rem-th largest
+// of the counted keys falls (sh.digit), the keys in larger ones (sh.above) and
+// in it (sh.here).  Thread t holds the t-th pair of bins from the top.
+__device__ __forceinline__ void topk_digit(const uint32_t* hist, uint32_t rem, TopkShared& sh,
+                                           int tid, int lane, int wave) {
+  const uint32_t h0 = hist[kTopkBins - 1 - 2 * tid], h1 = hist[kTopkBins - 2 - 2 * tid];
+  const uint32_t incl = wave_scan(h0 + h1);
+  if (lane == 63) sh.wave_a[wave] = incl;
+  __syncthreads();
+  const uint32_t excl = waves_before(sh.wave_a, lane, wave) + incl - (h0 + h1);
+  if (excl < rem && rem <= excl + h0 + h1) {
+    const bool second = excl + h0 < rem;
+    sh.digit = static_cast<uint32_t>(kTopkBins - 1 - 2 * tid - (second ? 1 : 0));
+    sh.above = second ? excl + h0 : excl;
+    sh.here = second ? h1 : h0;
+  }
+  __syncthreads();
+}
+
+// The selection of matrix d.  WORDS > 0: a wave's words (at most WORDS) are
+// held in registers; 0: any number of columns, the keys read again each time.
+template <int WORDS>
+__device__ __forceinline__ void topk_block(const DevMat& d, TopkShared& sh) {
+  const int64_t m = d.m, k = d.k;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const float* __restrict__ s = d.norms;
+  const int wave = uniform_i32(tid >> 6);
+  const int32_t words = static_cast<int32_t>((m + 63) >> 6);
+  const int32_t per = (words + kTopkWaves - 1) / kTopkWaves;
+  const int32_t w0 = min(wave * per, words);
+  const int32_t nw = min(per, words - w0);  // this wave's words
+  // word i holds this lane's column iff 64 * i < left
+  const int32_t left = static_cast<int32_t>(m) - w0 * 64 - lane;
+  const float* __restrict__ sw = d.norms + (static_cast<int64_t>(w0) * 64 + lane);
 
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t sh_wave[kTopkThreads / 64];
-  __shared__ uint32_t sh_digit, sh_above;
+  // A lane without a column holds key 0, the smallest: it changes neither the
+  // k-th largest key nor how many keys lie above it.
+  uint32_t reg[WORDS > 0 ? WORDS : 1];
+  float x[WORDS > 0 ? WORDS : 1];
+  if constexpr (WORDS > 0) {
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) x[i] = (i < nw && 64 * i < left) ? sw[64 * i] : 0.0f;
+  }
+  for (int b = tid; b < 3 * kTopkBins; b += kTopkThreads) (&sh.hist[0][0])[b] = 0u;
+  if (tid == 0) sh.digit = sh.above = sh.here = 0u;
+  if constexpr (WORDS > 0) {
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) reg[i] = 64 * i < left ? order_key(x[i]) : 0u;
+  }
+  // fn(i, key) over the wave's words
+  const auto each = [&](auto fn) {
+    if constexpr (WORDS > 0) {
+#pragma unroll
+      for (int i = 0; i < WORDS; ++i)
+        if (i < nw) fn(i, reg[i]);
+    } else {
+      for (int32_t i = 0; i < nw; ++i)
+        fn(i, 64 * i < left ? order_key(sw[64 * static_cast<int64_t>(i)]) : 0u);
+    }
+  };
 
+  // taken: the keys above thr, and the first `need` equal to it
   uint32_t thr, need;
   if (k == 0) {
     thr = 0xffffffffu;
@@ -202,89 +267,108 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const DevMat* __rest
     thr = 0u;
     need = static_cast<uint32_t>(m);
   } else {
-    uint32_t prefix = 0u, pmask = 0u, rem = static_cast<uint32_t>(k);
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) hist[tid] = 0u;
-      if (tid == 0) {
-        sh_digit = 0u;
-        sh_above = 0u;
-      }
+    uint32_t rem = static_cast<uint32_t>(k);
+    __syncthreads();
+    each([&](int, uint32_t key) { atomicAdd(&sh.hist[0][key >> 21], 1u); });
+    __syncthreads();
+    topk_digit(sh.hist[0], rem, sh, tid, lane, wave);
+    uint32_t prefix = sh.digit;
+    rem -= sh.above;
+    uint32_t here = sh.here;
+    int bits = 11;  // of the key in prefix
+#pragma unroll 1
+    for (int pass = 1; pass < 3 && (here != rem || prefix == 0u); ++pass) {
+      // (the next write of digit, above and here comes after two barriers)
+      const int next = pass == 1 ? 11 : 10;
+      uint32_t* hist = sh.hist[pass];
+      each([&](int, uint32_t key) {
+        if ((key >> (32 - bits)) == prefix)
+          atomicAdd(&hist[(key >> (32 - bits - next)) & ((1u << next) - 1u)], 1u);
+      });
       __syncthreads();
-      for (int64_t j = tid; j < m; j += kTopkThreads) {
-        const uint32_t key = order_key(s[j]);
-        if ((key & pmask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        // lane l holds bins 255-4l .. 252-4l (descending digit order)
-        uint32_t h[4], tot = 0u;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          h[c] = hist[255 - 4 * lane - c];
-          tot += h[c];
-        }
-        uint32_t incl = tot;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const uint32_t v = __shfl_up(incl, off, 64);
-          if (lane >= off) incl += v;
-        }
-        const uint32_t excl = incl - tot;
-        if (excl < rem && rem <= incl) {
-          uint32_t run = excl;
-          for (int c = 0; c < 4; ++c) {
-            if (run + h[c] >= rem) {
-              sh_digit = static_cast<uint32_t>(255 - 4 * lane - c);
-              sh_above = run;
-              break;
-            }
-            run += h[c];
-          }
-        }
-      }
-      __syncthreads();
-      const uint32_t digit = sh_digit;
-      rem -= sh_above;
-      prefix |= digit << shift;
-      pmask |= 255u << shift;
-      __syncthreads();
+      topk_digit(hist, rem, sh, tid, lane, wave);
+      prefix = (prefix << next) | sh.digit;
+      rem -= sh.above;
+      here = sh.here;
+      bits += next;
     }
-    thr = prefix;
-    need = rem;
+    const uint32_t low = prefix << (32 - bits);  // smallest key with these digits
+    if (here == rem && low != 0u) {  // all of them are taken
+      thr = low - 1u;
+      need = 0u;
+    } else {  // (all 32 bits known)
+      thr = low;
+      need = rem;
+    }
   }
 
-  const int64_t words = (m + 63) >> 6;
-  uint32_t carry_sel = 0u, carry_eq = 0u;
-  for (int64_t base = 0; base < m; base += kTopkThreads) {
-    const int64_t j = base + tid;
-    const bool valid = j < m;
-    const uint32_t key = valid ? order_key(s[j]) : 0u;
-    const bool gt = valid && key > thr;
-    const bool eq = valid && key == thr;
-    uint32_t eq_total, eq_wave_before, sel_total, sel_wave_before;
-    uint64_t eq_ballot, sel_ballot;
-    const uint32_t eq_rank =
-        carry_eq + block_excl_count(eq, sh_wave, &eq_total, &eq_wave_before, &eq_ballot);
-    const bool take = gt || (eq && eq_rank < need);
-    const uint32_t sel_rank =
-        carry_sel + block_excl_count(take, sh_wave, &sel_total, &sel_wave_before, &sel_ballot);
+  // what the wave holds above the threshold and at it
+  uint32_t gt = 0u, eq = 0u;
+  each([&](int i, uint32_t key) {
+    gt += __popcll(__ballot(key > thr));
+    if (need != 0u) eq += __popcll(__ballot(key == thr && 64 * i < left));
+  });
+  __syncthreads();  // (the last digit's wave sums are read)
+  if (lane == 0) {
+    sh.wave_a[wave] = gt;
+    sh.wave_b[wave] = eq;
+  }
+  __syncthreads();
+  uint32_t carry_eq = waves_before(sh.wave_b, lane, wave);
+  uint32_t carry_sel = waves_before(sh.wave_a, lane, wave) + min(carry_eq, need);
+  uint64_t my_mask = 0u;
+  int32_t my_prefix = 0;
+  int32_t* __restrict__ out_sel = d.sel_idx;
+  int32_t* __restrict__ out_uns = d.unsel_idx;
+  const uint32_t n_sel = static_cast<uint32_t>(k), n_uns = static_cast<uint32_t>(m - k);
+  each([&](int i, uint32_t key) {
+    bool take = key > thr;
+    if (need != 0u) {
+      const uint64_t b_eq = __ballot(key == thr && 64 * i < left);
+      take = take || (key == thr && 64 * i < left && carry_eq + lanes_below(b_eq) < need);
+      carry_eq += static_cast<uint32_t>(__popcll(b_eq));
+    }
+    const uint64_t b_sel = __ballot(take);
+    const uint32_t rank = carry_sel + lanes_below(b_sel);
+    const uint32_t j = static_cast<uint32_t>((w0 + i) * 64 + lane);
     // The ranks are in range whenever the select above is right; the guards
     // keep a wrong count from ever writing outside the outputs.
-    if (valid) {
-      if (take) {
-        if (sel_rank < static_cast<uint32_t>(k)) d.sel_idx[sel_rank] = static_cast<int32_t>(j);
-      } else if (j - sel_rank < m - k) {
-        d.unsel_idx[j - sel_rank] = static_cast<int32_t>(j);
+    int32_t* to = take ? out_sel : out_uns;
+    const uint32_t at = take ? rank : j - rank;
+    if (64 * i < left && at < (take ? n_sel : n_uns)) to[at] = static_cast<int32_t>(j);
+    if constexpr (WORDS > 0) {
+      if (lane == i) {
+        my_mask = b_sel;
+        my_prefix = static_cast<int32_t>(carry_sel);
       }
+    } else if (lane == 0) {
+      d.mask[w0 + i] = b_sel;
+      d.prefix[w0 + i] = static_cast<int32_t>(carry_sel);
     }
-    const int64_t w = (base >> 6) + wave;
-    if (lane == 0 && w < words) {
-      d.mask[w] = sel_ballot;
-      d.prefix[w] = static_cast<int32_t>(carry_sel + sel_wave_before);
+    carry_sel += static_cast<uint32_t>(__popcll(b_sel));
+  });
+  if constexpr (WORDS > 0) {
+    if (lane < nw) {
+      d.mask[w0 + lane] = my_mask;
+      d.prefix[w0 + lane] = my_prefix;
     }
-    carry_sel += sel_total;
-    carry_eq += eq_total;
   }
+}
+
+template <bool BATCHED>
+__global__ __launch_bounds__(kTopkThreads) void topk_kernel(const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one) {
+  int64_t local;
+  const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
+  __shared__ TopkShared sh;
+  if (d.m == 0) return;
+  // the words a wave owns decide the variant (unrolled over that many)
+  const int64_t per = (((d.m + 63) >> 6) + kTopkWaves - 1) / kTopkWaves;
+  if (per <= 1) topk_block<1>(d, sh);
+  else if (per <= 4) topk_block<4>(d, sh);
+  else if (per <= 8) topk_block<8>(d, sh);
+  else if (per <= 16) topk_block<16>(d, sh);
+  else if (per <= kTopkMaxWords) topk_block<kTopkMaxWords>(d, sh);
+  else topk_block<0>(d, sh);
 }
 
 // ---------------------------------------------------------------------------

@@ -23,7 +23,7 @@
 // accumulated buffer; a block sums the squares of 256 virtual columns over
 // one row block (the column-score row blocks) in fp64 and stores one
 // partial per column and row block in the plan's column-score workspace;
-// the row-major finalize adds them in row-block order.
+// the row-major finalize adds them in a fixed order.
 #include "zf_device.hpp"
 
 namespace zf {
