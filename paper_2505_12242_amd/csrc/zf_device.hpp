@@ -49,32 +49,68 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 }
 
 // Workgroups are dispatched to the 8 XCDs of the chip round-robin by block
-// id.  Remapping the id so that XCD x handles one contiguous range of the
-// grid gives each XCD (and its L2) a contiguous address stream, which
-// measured 4-5% faster for the streaming passes.  A bijection on [0, B) for
-// any B (the first B mod 8 XCDs take one block more).
+// id.  The id is remapped so that, within each window of 8 * RUN blocks, XCD x
+// handles RUN consecutive ones (a power of two; the blocks after the last full
+// window, or the whole grid where RUN is 0, are split into one contiguous
+// range per XCD): each XCD and its L2 stream contiguous addresses.  A bijection
+// on [0, B) for any B.
+//
+// One range per XCD (4-5% faster than no remapping) hands whole matrices to an
+// XCD when the set is small, and the matrices' blocks differ in work: a score
+// wave's channel is as long as its matrix has rows.  Windows balance that, and
+// keep the XCDs in one neighbourhood of every stream; over tens of GB a pass
+// separate ranges are the faster again.  Measured, RUN 64 / 256 / one range, in
+// us:
+//   column scores        7B layer 66 / 64 / 89, 70B layer 252 / 253 / 460, two
+//                        embeddings and 12 7B layers (118 K blocks) 797 / 785 /
+//                        868, ten 70B layers (195 K) 2600 / - / 2510; with the
+//                        hand-over, 13B layer (11 K) 361 / 384 / 502, the 13B set
+//                        (460 K) 13200 / 13100 / 12530
+//   hand-over, deferred  7B layer (52 K blocks) 423 / 430 / 441, 3 layers and
+//                        embeddings (220 K) 2210 / 2190 / 2196, 12 (690 K) 6915 /
+//                        6757 / 6778, 20 (1.1 M) 11170 / 10930 / 10900
+//   row-major update     7B layer (15 K larger blocks) 696 / 700 / 727, the 7B
+//                        set's deferred hand-over (490 K) - / 23300 / 22400
+//   Adam, selected grid  13B layer (79 K) 457 / 451 / 469, 70B (84 K) 450 / 436 /
+//                        440, 12 7B layers (265 K) 1405 / 1383 / 1381, 20 (430 K)
+//                        2273 / 2240 / 2222
+// (runs of 16 are within 2% of 64; 1024 lose the balance).
 #ifndef ZF_XCD_REMAP
 #define ZF_XCD_REMAP 1
 #endif
-constexpr int kXcds = 8;
+constexpr uint32_t kXcds = 8;
 
-__device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t B) {
+enum XcdOrder { kOrderScores, kOrderStream, kOrderSelected, kOrderRowMajor };
+
+template <int ORDER = kOrderStream>
+__device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B) {
   if constexpr (ZF_XCD_REMAP == 0) return b;
-  const int64_t q = B / kXcds, r = B % kXcds;
-  const int64_t x = b % kXcds, i = b / kXcds;
-  return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
+  uint32_t lg;  // log2 RUN, or 0: one range per XCD
+  if constexpr (ORDER == kOrderScores) lg = B <= (1u << 17) ? 6 : 0;
+  else if constexpr (ORDER == kOrderRowMajor) lg = B <= (1u << 17) ? 6 : 0;
+  else if constexpr (ORDER == kOrderSelected) lg = B <= (1u << 18) ? 8 : 0;
+  else lg = B <= (1u << 17) ? 6 : B <= (1u << 20) ? 8 : 0;
+  const uint32_t full = lg != 0 ? B >> (lg + 3) << (lg + 3) : 0;
+  if (b < full) {
+    const uint32_t i = b & ((kXcds << lg) - 1);
+    return b - i + ((i % kXcds) << lg) + i / kXcds;
+  }
+  const uint32_t rest = B - full, t = b - full;
+  const uint32_t q = rest / kXcds, r = rest % kXcds;
+  const uint32_t x = t % kXcds, i = t / kXcds;
+  return full + (x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i);
 }
 
 // Descriptor of the matrix the (remapped) block belongs to.  BATCHED kernels
 // read it from the plan's device table (scalar loads); single-matrix kernels
 // take it by value.  Keeping the two apart avoids a generic pointer that
 // would turn the descriptor loads into flat vector loads.
-template <bool BATCHED>
+template <bool BATCHED, int ORDER = kOrderStream>
 __device__ __forceinline__ const DevMat& get_mat(const DevMat* __restrict__ mats,
                                                  const int64_t* __restrict__ off, int32_t nmats,
                                                  const DevMat& one, int64_t& local,
                                                  int32_t& index) {
-  const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t b = xcd_remap<ORDER>(blockIdx.x, gridDim.x);
   if constexpr (!BATCHED) {
     local = b;
     index = 0;
@@ -91,12 +127,12 @@ __device__ __forceinline__ const DevMat& get_mat(const DevMat* __restrict__ mats
   }
 }
 
-template <bool BATCHED>
+template <bool BATCHED, int ORDER = kOrderStream>
 __device__ __forceinline__ const DevMat& get_mat(const DevMat* __restrict__ mats,
                                                  const int64_t* __restrict__ off, int32_t nmats,
                                                  const DevMat& one, int64_t& local) {
   int32_t index;
-  return get_mat<BATCHED>(mats, off, nmats, one, local, index);
+  return get_mat<BATCHED, ORDER>(mats, off, nmats, one, local, index);
 }
 
 // Raw buffer resources (gfx9 family word 3).  A resource is based at the

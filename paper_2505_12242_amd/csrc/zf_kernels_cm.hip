@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
                                                              int32_t nmats, DevMat one,
                                                              float scale) {
   int64_t local;
-  const DevMat d = get_mat<BATCHED>(mats, off, nmats, one, local);
+  const DevMat& d = get_mat<BATCHED, kOrderScores>(mats, off, nmats, one, local);
   const int lane = threadIdx.x & 63;
   // the wave's channel, moved to scalar registers (it is wave-uniform, which
   // the compiler cannot tell from threadIdx.x; without this every buffer
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
   }
   int64_t local;
   int32_t q;
-  const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local, q);
+  const DevMat& d = get_mat<BATCHED, SELG ? kOrderSelected : kOrderStream>(mats, off, nmats, one, local, q);
   // SELG: one quad per lane, cm_snch chunks per channel; else cm_qpt quads
   const int32_t qpt = SELG ? 1 : d.cm_qpt;
   const int64_t nch = SELG ? d.cm_snch : d.cm_nch;
@@ -915,8 +915,7 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
   const bool from_stage = !DEFP && stage != 0 && length == 1;
   const int32_t kept = DEFP ? min(max(length - 1, 0), h.n) : 0;
   // each block walks one contiguous run of units, the runs in the
-  // XCD-aware block order (XCD x covers one contiguous range, as the
-  // full-grid passes do)
+  // XCD-aware block order
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t per = (units + gridDim.x - 1) / gridDim.x;
   const int64_t u0 = b * per;

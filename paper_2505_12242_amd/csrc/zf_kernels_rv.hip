@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   __shared__ __attribute__((aligned(16))) float sd[HAND ? kRvBatch : 1][HAND ? kRvMaxCols : 4];
 
   int64_t local;
-  const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
+  const DevMat& d = get_mat<BATCHED, kOrderRowMajor>(mats, off, nmats, one, local);
   const int32_t q = BATCHED ? static_cast<int32_t>(&d - mats) : 0;
   const int64_t cblk = local % d.rv_cb;
   const int64_t rblk = local / d.rv_cb;
