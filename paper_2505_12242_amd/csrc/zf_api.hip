@@ -144,8 +144,15 @@ int pick_update_rows(const std::vector<std::pair<int64_t, int64_t>>& shapes) {
 #define ZF_RV_ENABLE 1
 #endif
 
+// Widths are multiples of 64 columns where that needs no more tiles: the tiles
+// then meet at 128-byte boundaries of G and W (rows of 64-column multiples), so
+// no line is shared between two blocks.  Measured on a Llama-2-7B layer, 832 and
+// 960 columns against 824 and 920: in-place update 696 -> 685 us, with the stage
+// 622 -> 606, with the hand-over 711 -> 698.
 int32_t rv_width(int64_t m) {
   const int64_t tiles = std::max<int64_t>(1, ceil_div(m, zf::kRvMaxCols));
+  const int64_t w64 = 64 * ceil_div(std::max<int64_t>(m, 1), 64 * tiles);
+  if (w64 <= zf::kRvMaxCols) return static_cast<int32_t>(w64);
   return static_cast<int32_t>(8 * ceil_div(std::max<int64_t>(m, 1), 8 * tiles));
 }
 
