@@ -626,14 +626,14 @@ typedef struct zf_zen_totals {
  * 1/step_in_interval) when trigger is set; the next step then starts a new
  * interval (step_in_interval = 1).
  * Channel-major plans sum the squares inside the update pass.  Row-major
- * plans do too on steps with the states in place when their buffers take
- * the 16-byte update (see Layouts); on refresh steps, and for other
- * buffers, they run the update and then a separate statistics pass that
- * reads the selected gradient columns and the packed buffer again.  Both
- * row-major forms write the same fp64 partials (per column and
- * column-score row block, in row order) to the plan's column-score
- * workspace, so they give identical statistics; the two layouts agree up to
- * the order of the fp64 sums.
+ * plans do too when their buffers take the 16-byte update (see Layouts;
+ * on refresh steps the packing pass sums them, after the Adam pass); for
+ * other buffers, and with the owed deferred update, they run the update and
+ * then a separate statistics pass that reads the selected gradient columns
+ * and the packed buffer again.  Both row-major forms write the same fp64
+ * partials (per column and row block, in row order) to the plan's
+ * column-score workspace, so they give identical statistics; the two layouts
+ * agree up to the order of the fp64 sums.
  * Requirements: every descriptor of the plan provides sel_sq [k] and
  * acc_sq [m - k] (device fp32, disjoint from each other and from the
  * update's buffers), tau >= 0 (+inf allowed, never triggers when

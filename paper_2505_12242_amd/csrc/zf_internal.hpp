@@ -118,7 +118,8 @@ struct DevMat {
   int32_t rv;        // row-major: the 16-byte update kernel is used (else per-column)
   int32_t rv_w;      // row-major 16-byte update: tile width (columns)
   int32_t rv_cb;     // row-major 16-byte update: column tiles
-  int32_t rv_rows;   // row-major 16-byte update: rows per block
+  int32_t rv_rows;   // row-major 16-byte update and Zen-auto statistics: rows per block
+  int32_t zn_rb;     // row-major Zen-auto statistics: row blocks (of rv_rows rows)
 };
 
 // Per-kernel view of a batch: a device array of matrices and the first
@@ -189,7 +190,7 @@ hipError_t launch_unpack_zen(const Table& t, int64_t units, const ZenState* zst,
 
 // Row-major update with 16-byte accesses (zf_kernels_rv.hip); same contract
 // as launch_update, geometry rv_w / rv_cb / rv_rows.  zs != nullptr (fused
-// update only, rv_rows == cn_rpb): also the Zen-auto partials of the
+// update or packing): also the Zen-auto partials of the
 // row-major statistics pass, into zs at each matrix's cn_ws.
 hipError_t launch_rv_update(const Table& t, const DevMat& one, int64_t blocks, const AdamK& c,
                             int32_t mode, int32_t first, bool adam, bool pack, bool handover,

@@ -938,15 +938,19 @@ hipError_t launch_unpack(const Table& t, const DevMat& one, int64_t blocks, floa
   return hipGetLastError();
 }
 
-// 256 blocks per CU: a step that does not end its interval exits in a
-// short launch, one that does keeps enough tiles in flight (4096 and a full
-// grid measured slower)
-constexpr int64_t kUnpackZenGrid = 65536;
+// A step that does not end its interval should exit in a short launch, one
+// that does keep enough tiles in flight.  On a Llama-2-7B layer (98.8 K tiles)
+// 65536 blocks take 15.3 us to exit and 292 us to hand over, 16384 5.0 and 305,
+// 4096 4.9 and 330: eight tiles a block from 16384 blocks on, and 65536 for the
+// large sets, where a hand-over takes milliseconds and 10 us do not count.
+constexpr int64_t kUnpackZenMin = 16384, kUnpackZenMax = 65536;
 
 hipError_t launch_unpack_zen(const Table& t, int64_t units, const ZenState* zst, hipStream_t s) {
   (void)hipGetLastError();
   if (units <= 0 || t.mats == nullptr) return hipSuccess;
-  const dim3 grid(static_cast<uint32_t>(units < kUnpackZenGrid ? units : kUnpackZenGrid));
+  const int64_t want = units / 8 < kUnpackZenMin ? kUnpackZenMin
+                       : units / 8 > kUnpackZenMax ? kUnpackZenMax : units / 8;
+  const dim3 grid(static_cast<uint32_t>(units < want ? units : want));
   hipLaunchKernelGGL(unpack_zen_kernel, grid, dim3(kThreads), 0, s, t.mats, t.off, t.nmats, units,
                      zst);
   return hipGetLastError();

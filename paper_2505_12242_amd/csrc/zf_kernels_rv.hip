@@ -27,10 +27,10 @@
 //     most 254 lanes and an Adam lane holds at most 4 slots (checked for
 //     every tile width, slot alignment and selected count).
 // Rows are staged kRvBatch at a time, every load of a batch issued before
-// the first wait.  The kernel serves steps with the compact states in place
-// (and pack-only calls); a refresh step, whose entering and leaving columns
-// read and write their sources element by element, runs the per-column
-// kernel.
+// the first wait.  The Adam part serves steps with the compact states in place;
+// on a refresh step, whose entering and leaving columns read and write their
+// sources element by element, the per-column kernel runs Adam alone and this
+// one the packing (and the statistics, and the hand-over).
 //
 // The bf16 first-step stage (acc1, optional; one bf16 row per gradient row):
 // on an interval's first step (first == 1) the block stores the G rows it
@@ -39,7 +39,7 @@
 // are loaded and staged in LDS like G, and the pack lanes take their
 // previous values from there instead of from A.
 //
-// STATS (Zen-auto, blocks of cn_rpb rows; with HAND on an end the caller
+// STATS (Zen-auto; with HAND on an end the caller
 // forces, the sums before the scale): each lane also sums, in fp64 and
 // in row order, the squares of its selected columns' gradient and of its
 // unselected slots' new accumulated values over the block's rows, and
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
                                                              double* __restrict__ zs,
                                                              HistTable hist,
                                                              const ZenState* __restrict__ zst) {
-  static_assert(!STATS || (ADAM && PACK), "statistics of the fused update");
+  static_assert(!STATS || PACK, "statistics of the packing pass");
   static_assert(!DEF || (BATCHED && !ADAM && !PACK && !HAND && !STATS && !A16),
                 "the deferred hand-over pass");
   // Zen-auto with the interval driven on the device (steps in place):
@@ -169,7 +169,9 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   const int tid = threadIdx.x;
   const bool is_q = tid < nqf;
   const bool is_e = !is_q && tid < nqf + ne;
-  const bool is_s = ADAM && tid >= nqf + ne && cs > 0;
+  // (without ADAM the selected slots' lanes take the statistics of their
+  // gradient and zero the hand-over at their columns)
+  const bool is_s = (ADAM || STATS || HAND) && tid >= nqf + ne && cs > 0;
 
   // The lane's elements: slot s[e] (byte offset vs[e] in its buffer's
   // row), column offset cj[e] in the tile, valid bit e.
@@ -478,7 +480,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
           }
         }
       }
-    } else if (ADAM && is_s) {
+    } else if (is_s) {
 #pragma unroll
       for (int b = 0; b < kRvBatch; ++b) {
         if (b < nb) {
@@ -492,12 +494,14 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
                 const double x = static_cast<double>(g);
                 zq[e] = __builtin_fma(x, x, zq[e]);
               }
-              adam_step(g, x0[b][e], x1[b][e], x2[b][e], c);
-              buf_put_f32(x0[b][e], rP, vs[e], so);
-              buf_put_f32(x1[b][e], rM, vs[e], so);
-              buf_put_f32(x2[b][e], rV, vs[e], so);
-              buf_put_u16<kStream>(round_bf16(x0[b][e]), rW,
-                                   static_cast<uint32_t>(c0 + cj[e]) * 2u, sw);
+              if constexpr (ADAM) {
+                adam_step(g, x0[b][e], x1[b][e], x2[b][e], c);
+                buf_put_f32(x0[b][e], rP, vs[e], so);
+                buf_put_f32(x1[b][e], rM, vs[e], so);
+                buf_put_f32(x2[b][e], rV, vs[e], so);
+                buf_put_u16<kStream>(round_bf16(x0[b][e]), rW,
+                                     static_cast<uint32_t>(c0 + cj[e]) * 2u, sw);
+              }
               if constexpr (HAND) sd[b][cj[e]] = 0.0f;  // hand-over: +0 at a selected column
             }
           }
@@ -527,7 +531,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   }
 
   if constexpr (STATS) {
-    // one partial per virtual column of this row block (rv_rows = cn_rpb)
+    // one partial per virtual column of this row block
     double* __restrict__ out = zs + d.cn_ws + rblk * d.m;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -576,14 +580,16 @@ hipError_t launch_rv_update(const Table& t, const DevMat& one, int64_t blocks, c
   (void)hipGetLastError();
   if (blocks <= 0) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  if (handover && !(adam && pack)) return hipErrorInvalidValue;
+  if ((handover || zs != nullptr) && !pack) return hipErrorInvalidValue;
   if (adam && mode != kInplace) return hipErrorInvalidValue;  // refresh: per-column kernel
-  if (zst != nullptr && zs == nullptr) return hipErrorInvalidValue;  // Zen-auto steps only
+  if (zst != nullptr && (zs == nullptr || !adam)) return hipErrorInvalidValue;  // Zen-auto steps only
   if (zs != nullptr) {
-    if (!(adam && pack) || (handover && zst == nullptr)) return hipErrorInvalidValue;
+    if (handover && (zst == nullptr || !adam)) return hipErrorInvalidValue;
     if (handover) launch_rv_t<true, true, true, true>(t, one, grid, c, first, 1.0f, s, zs, zst);
-    else launch_rv_t<true, true, false, true>(t, one, grid, c, first, 1.0f, s, zs, zst);
-  } else if (handover) launch_rv_t<true, true, true>(t, one, grid, c, first, scale, s);
+    else if (adam) launch_rv_t<true, true, false, true>(t, one, grid, c, first, 1.0f, s, zs, zst);
+    else launch_rv_t<false, true, false, true>(t, one, grid, c, first, 1.0f, s, zs);
+  } else if (handover && adam) launch_rv_t<true, true, true>(t, one, grid, c, first, scale, s);
+  else if (handover) launch_rv_t<false, true, true>(t, one, grid, c, first, scale, s);
   else if (adam && pack) launch_rv_t<true, true, false>(t, one, grid, c, first, 1.0f, s);
   else if (adam) launch_rv_t<true, false, false>(t, one, grid, c, first, 1.0f, s);
   else if (pack) launch_rv_t<false, true, false>(t, one, grid, c, first, 1.0f, s);

@@ -21,7 +21,7 @@
 // separate pass after the update: virtual column c < k is the selected
 // gradient column sel_idx[c], c >= k the packed column u = c - k of the
 // accumulated buffer; a block sums the squares of 256 virtual columns over
-// one row block (the column-score row blocks) in fp64 and stores one
+// one row block (those of the 16-byte update) in fp64 and stores one
 // partial per column and row block in the plan's column-score workspace;
 // the row-major finalize adds them in a fixed order.
 #include "zf_device.hpp"
@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kZenCols) void rm_zen_partial_kernel(const DevMat* 
   const int64_t rblk = local / cb;
   const int64_t c = (local % cb) * kZenCols + threadIdx.x;
   if (c >= d.m) return;
-  const int64_t i0 = rblk * d.cn_rpb;
-  const int64_t i1 = min(i0 + static_cast<int64_t>(d.cn_rpb), d.n);
+  const int64_t i0 = rblk * d.rv_rows;
+  const int64_t i1 = min(i0 + static_cast<int64_t>(d.rv_rows), d.n);
   double s = 0.0;
   if (c < d.k) {
     const uint16_t* __restrict__ g = d.grad + d.sel_idx[c];
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kFinThreads) void rm_zen_finalize_kernel(
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t c = local * kFinCols + (threadIdx.x & 63);
   __shared__ double red[kFinSegs][kFinCols];
-  const double s = finalize_sum(zs + d.cn_ws, d.cn_rb, d.m, c, red);
+  const double s = finalize_sum(zs + d.cn_ws, d.zn_rb, d.m, c, red);
   if (threadIdx.x >= kFinCols) return;
   double root_sel = 0.0, root_acc = 0.0;
   if (c < d.m) {

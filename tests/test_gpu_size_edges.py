@@ -63,3 +63,50 @@ def test_selection_variants(m, kind):
         assert np.array_equal(got.unsel_idx.cpu().numpy(), want.unsel), (m, kind, ratio)
         assert np.array_equal(mask_np(got.mask), want.mask), (m, kind, ratio)
         assert np.array_equal(got.prefix.cpu().numpy(), want.prefix), (m, kind, ratio)
+
+
+# Row-major Zen-auto: the 16-byte update with its statistics (and on a refresh
+# the packing pass with them, after the per-column Adam) against the
+# per-column update with the separate statistics pass, which buffers off the
+# 16-byte path run.  Same fp64 partials in the same order: identical bits.
+# Rows at the edges of the row batches and row blocks, columns at the edges of
+# the tiles (multiples of 64 up to 960, else of 8 up to 1000).
+@pytest.mark.parametrize("n", [1, 15, 17, 129])
+@pytest.mark.parametrize("m", [8, 960, 961, 1000, 1921])
+def test_row_major_zen_paths_agree(n, m):
+    k = zf.k_from_ratio(0.1, m)
+    dev = torch.device("cuda")
+    rng = np.random.default_rng(n + 7 * m)
+    g = [gbits(n, m, 11 * n + m + t) for t in range(3)]
+    w0 = O.bf16_round((0.02 * rng.standard_normal((n, m))).astype(np.float32))
+    master = torch.from_numpy(rng.standard_normal((n, m)).astype(np.float32)).to(dev)
+    scores = [torch.from_numpy(rng.random(m).astype(np.float32)).to(dev) for _ in range(2)]
+    got = []
+    for aligned in (True, False):
+        def bf16(b):
+            return bf16_dev(b, ld=-(-m // 8) * 8) if aligned else bf16_dev(b, offset=1)
+
+        sels = [zf.topk_select(s, 0.1) for s in scores]
+        w = bf16(w0)
+        acc = zf.alloc_stored(zf.ROW_MAJOR, n, m - k)
+        st = [[zf.alloc_stored(zf.ROW_MAJOR, n, k) for _ in range(3)] for _ in range(2)]
+        sq = torch.zeros(k, device=dev), torch.zeros(m - k, device=dev)
+        totals = torch.zeros(zf.ZEN_TOTALS_BYTES // 8, dtype=torch.int64, device=dev)
+        out = []
+        # init, in place, remap (from the master) to another selection
+        for t, (mode, p) in enumerate([(zf.STATES_INIT, 0), (zf.STATES_INPLACE, 0),
+                                       (zf.STATES_REMAP, 1)]):
+            src = zf.StateSource(prev=sels[1 - p], prev_master=st[1 - p][0],
+                                 prev_exp_avg=st[1 - p][1], prev_exp_avg_sq=st[1 - p][2],
+                                 init_master=master)
+            plan = zf.Plan([zf.MatrixBuffers(
+                grad=bf16(g[t]), k=k, sel=sels[p], weight=w, master=st[p][0], exp_avg=st[p][1],
+                exp_avg_sq=st[p][2], acc=acc, src=src, sel_sq=sq[0], acc_sq=sq[1])])
+            plan.update_zen(zf.AdamHparams(lr=1e-3), t + 1, mode, 1 + (t == 1), 4, 1.0, totals)
+            torch.cuda.synchronize()
+            out += [x.clone() for x in (w, acc, *st[p], *sq, totals)]
+            plan.close()
+        got.append(out)
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a,
+                           b.view(torch.int16) if b.dtype == torch.bfloat16 else b), (n, m, i)
