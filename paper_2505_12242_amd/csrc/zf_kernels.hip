@@ -510,13 +510,28 @@ __device__ __forceinline__ void load_state(const AdamSrc& a, int32_t i, float& p
         adam_step(buf_f32(a.rPA, a.vPA, i * a.sPA) * pd->scale, p, m, v, pd->c);
     }
   } else {
+    // A column that stays reads its previous states, an entering one the fp32
+    // master: only the lanes that need a master line touch it (reading both and keeping
+    // one took 494 us against 324 for the Adam pass of a Llama-2-7B layer's
+    // refresh: almost every line of a 4-byte master holds a selected column).
+    if constexpr (SRC == kSrcRemapMaster) {
+      if (a.was) {
+        p = buf_f32(a.rSP, a.vPrev, i * a.sPrev);
+        m = buf_f32(a.rSM, a.vPrev, i * a.sPrev);
+        v = buf_f32(a.rSV, a.vPrev, i * a.sPrev);
+      } else {
+        p = buf_f32(a.rI, a.vI, i * a.sI);
+        m = v = 0.0f;
+      }
+      return;
+    }
     // init value of p for a newly selected column
     float pi;
-    if constexpr (SRC == kSrcRemapMaster || SRC == kSrcInitMaster)
+    if constexpr (SRC == kSrcInitMaster)
       pi = buf_f32(a.rI, a.vI, i * a.sI);
     else
       pi = widen_bf16(buf_u16(a.rW, a.vG, i * a.sW));
-    if constexpr (SRC == kSrcRemapW || SRC == kSrcRemapMaster) {
+    if constexpr (SRC == kSrcRemapW) {
       // both sources are read; the lane keeps the one that applies
       const float pp = buf_f32(a.rSP, a.vPrev, i * a.sPrev);
       const float mp = buf_f32(a.rSM, a.vPrev, i * a.sPrev);
