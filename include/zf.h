@@ -58,10 +58,9 @@
  *           (row r = column sel_idx[r]), A is [m-k][ld_acc >= n] (row u =
  *           column unsel_idx[u]).  Results are identical in both layouts.
  *           Row-major update steps with the states in place (and pack-only
- *           calls) run a kernel with 16-byte accesses when G is 16-byte
- *           aligned with ld % 8 == 0 and A, P/M/V and the hand-over output
- *           (those the call uses) are 16-byte aligned with ld % 4 == 0;
- *           otherwise a per-column kernel.  The results are identical.
+ *           calls) run a kernel with 16-byte accesses, refresh steps (and
+ *           Adam-only steps of small matrices whose gradient rows are not
+ *           16-byte aligned) a per-column kernel.  The results are identical.
  * Selection.  sel_idx[k] and unsel_idx[m-k] are ascending column indices;
  *           sel_mask[ceil(m/64)] has bit b of word w set iff column 64w+b is
  *           selected (bits at columns >= m are 0); sel_prefix[ceil(m/64)]
@@ -545,8 +544,8 @@ zf_status zf_plan_update_handover(zf_plan* plan, const zf_adam_hparams* hp, int6
  * those gradients are read.  They must not overlap what this step writes.
  * Both layouts, plans without a full-state store; `unpacked` required;
  * scale finite.  Row-major: two launches, the Adam-only pass and a
- * hand-over pass (the 16-byte kernels when the plan runs the 16-byte update
- * and every earlier gradient has 16-byte rows, else the per-column ones);
+ * hand-over pass (the 16-byte kernels unless a row stride is too long for
+ * them);
  * the hand-over pass reads every element of each step's gradient, since
  * the selected columns share their cache lines.  ZF_EINVAL (nothing
  * enqueued) on a mismatch or when an earlier gradient's row stride does
@@ -626,11 +625,11 @@ typedef struct zf_zen_totals {
  * 1/step_in_interval) when trigger is set; the next step then starts a new
  * interval (step_in_interval = 1).
  * Channel-major plans sum the squares inside the update pass.  Row-major
- * plans do too when their buffers take the 16-byte update (see Layouts;
- * on refresh steps the packing pass sums them, after the Adam pass); for
- * other buffers, and with the owed deferred update, they run the update and
- * then a separate statistics pass that reads the selected gradient columns
- * and the packed buffer again.  Both row-major forms write the same fp64
+ * plans do too (on refresh steps the packing pass sums them, after the Adam
+ * pass), but for row strides too long for the 16-byte update, and with the
+ * owed deferred update, where they run the update and then a separate
+ * statistics pass that reads the selected gradient columns and the packed
+ * buffer again.  Both row-major forms write the same fp64
  * partials (per column and row block, in row order) to the plan's
  * column-score workspace, so they give identical statistics; the two layouts
  * agree up to the order of the fp64 sums.

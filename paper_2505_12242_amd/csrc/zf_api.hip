@@ -137,9 +137,14 @@ int pick_update_rows(const std::vector<std::pair<int64_t, int64_t>>& shapes) {
 // Row-major update with 16-byte accesses: equal-width column tiles of at
 // most kRvMaxCols columns (multiples of 8, so that 16-byte G loads and
 // hand-over stores stay aligned) and rv_rows rows per block.
+// 16 rows per block on large grids; 8 up to kRvLargeBlocks blocks of 16, where
+// more blocks spread better: Llama-2-7B layer (15 K blocks), 16 / 8 rows, in us:
+// second step 603 / 588, in place 680 / 664, hand-over 699 / 684; the 7B set
+// (490 K) in ms: 16.1 / 16.3, 17.5 / 17.9, 18.2 / 18.6.
 #ifndef ZF_RV_ROWS
 #define ZF_RV_ROWS 16
 #endif
+constexpr int64_t kRvLargeBlocks = 1 << 16;
 #ifndef ZF_RV_ENABLE
 #define ZF_RV_ENABLE 1
 #endif
@@ -168,6 +173,10 @@ int pick_rv_rows(const std::vector<std::pair<int64_t, int64_t>>& shapes) {
     for (auto& s : shapes) total += rv_blocks(s.first, s.second, rows);
     if (total > kMaxBlocks && rows < (1 << 20)) {
       rows <<= 1;
+      continue;
+    }
+    if (rows == ZF_RV_ROWS && total <= kRvLargeBlocks) {
+      rows >>= 1;
       continue;
     }
     if (total >= kMinBlocks || rows <= 4) return rows;
@@ -388,19 +397,12 @@ bool cm_vec_ok(const DevMat& d) {
          ok(d.acc1, d.ld_acc1, 8);
 }
 
-// Row-major 16-byte update: G rows 16-byte aligned (8 bf16), and every
-// fp32 buffer moved in slot quads or column quads (A, P/M/V, the hand-over
-// output) 16-byte aligned per row.  Other buffers are accessed by element.
+// Row-major 16-byte update: any gradient rows (16-byte loads of any alignment);
+// the fp32 buffers moved in slot quads or column quads (A, P/M/V, the hand-over
+// output) in 16-byte accesses at 4-byte alignment.  Other buffers are accessed
+// by element.
 bool rv_ok(const DevMat& d) {
-  if (!ZF_RV_ENABLE || d.layout != zf::kRowMajor) return false;
-  // (a single row never uses its stride)
-  const bool one_row = d.n <= 1;
-  const auto ok = [one_row](const void* p, int64_t ld, int64_t per16) {
-    return p == nullptr || (aligned(p, 16) && (one_row || ld % per16 == 0));
-  };
-  return d.grad != nullptr && aligned(d.grad, 16) && (one_row || d.ld_grad % 8 == 0) &&
-         ok(d.acc, d.ld_acc, 4) && ok(d.P, d.ld_state, 4) && ok(d.M, d.ld_state, 4) &&
-         ok(d.V, d.ld_state, 4) && ok(d.out, d.ld_out, 4);
+  return ZF_RV_ENABLE && d.layout == zf::kRowMajor && d.grad != nullptr;
 }
 
 // Geometry of the row-major 16-byte update; used when `allow` (all matrices
@@ -473,10 +475,19 @@ int64_t unpack_grid(const DevMat& d) {
 // Row-major: the 16-byte kernel serves the steps without a refresh (states in
 // place, or no Adam); a refresh step (remap / init, whose per-column sources
 // it would read element by element behind a chain of dependent index loads)
-// runs the per-column kernel, which measured faster there.  Both give the
-// same bits.
-bool use_rv(const DevMat& one, int32_t mode, bool adam) {
-  return one.layout == zf::kRowMajor && one.rv && (!adam || mode == zf::kInplace);
+// runs the per-column kernel, which measured faster there.  Both give the same
+// bits.
+//
+// An Adam-only step whose gradient rows are not 16-byte aligned (g16 false)
+// runs the per-column kernel below kSmallAdam elements, which reads only the
+// selected columns' pieces of G: 4096 x 4095 24.2 against 33.1 us, 11008 x 4095
+// 77 against 70.
+constexpr int64_t kSmallAdam = int64_t(1) << 25;
+
+bool use_rv(const DevMat& one, int32_t mode, bool adam, bool pack, bool g16, int64_t elems) {
+  if (one.layout != zf::kRowMajor || !one.rv) return false;
+  if (adam && mode != zf::kInplace) return false;
+  return !(adam && !pack && !g16 && elems < kSmallAdam);
 }
 
 int64_t rv_grid(const DevMat& d) { return rv_blocks(d.n, d.m, d.rv_rows); }
@@ -562,7 +573,7 @@ zf_status run_update(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
   finish_geometry(d, 256, pick_update_rows({{n, m}}));
   set_rv(d, pick_rv_rows({{n, m}}), true);
   if (layout == zf::kRowMajor && !rm_strides_ok(d)) return ZF_EINVAL;
-  const bool rv = use_rv(d, mode, adam);
+  const bool rv = use_rv(d, mode, adam, pack, d.vec != 0, n * m);
   const int64_t blocks = rv ? rv_grid(d) : update_grid(d);
   if (blocks == 0) return ZF_OK;
   const hipError_t e = launch_update_any(single_table(), d, blocks, c, adam ? mode : 0,
@@ -857,7 +868,8 @@ struct zf_plan {
   double* d_zb = nullptr;  // Zen-auto per-finalize-block sums
   int64_t blk_cn = 0, blk_fin = 0, blk_top = 0, blk_up = 0, blk_unp = 0, blk_zen = 0, blk_zp = 0,
           blk_upv = 0, blk_sel = 0;
-  int64_t k_total = 0, u_total = 0;
+  int64_t k_total = 0, u_total = 0, elems = 0;
+  bool g16 = true;  // row-major: every gradient has 16-byte rows
   bool can_colnorm = true, can_topk = true, can_adam = true, can_remap = true, can_pack = true,
        can_unpack = true, can_zen = true, can_scatter = true, can_handover = true,
        can_pending = true, can_scatter_skip = true;
@@ -1047,6 +1059,8 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
     }
     p->k_total += d.k;
     p->u_total += d.m - d.k;
+    p->elems += d.n * d.m;
+    p->g16 = p->g16 && d.vec != 0;
     off_cn[q] = p->blk_cn;
     off_fin[q] = p->blk_fin;
     off_top[q] = p->blk_top;
@@ -1240,7 +1254,7 @@ hipError_t plan_update_launch(const zf_plan* p, const AdamK& c, int32_t mode, in
     const Table ts{p->d_mats, p->d_off_sel, p->nmats};
     return zf::launch_cm_adam_selected_grid(ts, p->mats[0], p->blk_sel, c, mode, s);
   }
-  const bool rv = use_rv(p->mats[0], mode, adam);
+  const bool rv = use_rv(p->mats[0], mode, adam, pack, p->g16, p->elems);
   const Table t{p->d_mats, rv ? p->d_off_upv : p->d_off_up, p->nmats};
   return launch_update_any(t, p->mats[0], rv ? p->blk_upv : p->blk_up, c, adam ? mode : 0, first,
                            adam, pack, p->layout, s, handover, scale, rv);
@@ -1354,9 +1368,7 @@ zf_status gather_earlier(const zf_plan* p, const zf_plan* const* earlier, int32_
         // through the same 32-bit offsets
         const int64_t lim = int64_t(1) << 31;
         if (b.n > 1 && a.ld_grad * 2 >= lim / std::max<int64_t>(b.up_rows, 1)) return ZF_EINVAL;
-        if (rv && !(aligned(a.grad, 16) && (b.n <= 1 || (a.ld_grad % 8 == 0 &&
-                                                          a.ld_grad * 2 < lim / b.rv_rows))))
-          rv = false;
+        if (rv && b.n > 1 && a.ld_grad * 2 >= lim / b.rv_rows) rv = false;
       }
       // an earlier gradient is only read: disjoint from everything the step writes
       const Span g = span(a.grad, ext(L, a.n, a.m), a.ld_grad, 2);
@@ -1459,7 +1471,7 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
   // force_end 2: the interval ends here and the update writes the hand-over
   // where it can (channel-major; row-major steps in place on the 16-byte
   // update); elsewhere a plain end, the hand-over left to the gated pass
-  const bool rv = p->layout == zf::kRowMajor && pd == nullptr && use_rv(p->mats[0], mode, true);
+  const bool rv = p->layout == zf::kRowMajor && pd == nullptr && use_rv(p->mats[0], mode, true, true, p->g16, p->elems);
   const bool fuse = force_end == 2 && p->can_handover && zst != nullptr &&
                     (p->layout == zf::kChannelMajor || rv);
   if (force_end == 2 && !fuse) force_end = 1;

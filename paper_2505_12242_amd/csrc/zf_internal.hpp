@@ -108,7 +108,8 @@ struct DevMat {
   int32_t up_rows;   // rows per update / unpack block
   int32_t up_rb;     // update row blocks
   int32_t up_cb;     // update column blocks
-  int32_t vec;       // 16-byte vector path allowed (alignment, strides, sizes)
+  int32_t vec;       // channel-major: vector path allowed (alignment, strides, sizes);
+                     // row-major: the gradient's rows are 16-byte aligned
   int32_t layout;    // Layout
   int32_t cm_nch;    // channel-major: row chunks per channel (update)
   int32_t cm_unch;   // channel-major: row chunks per channel (unpack)

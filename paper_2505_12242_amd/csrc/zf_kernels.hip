@@ -23,10 +23,8 @@ namespace {
 
 constexpr int kCnBatch = 4;  // rows per wave loaded before they are added
 
-// G is read once and the stage written once per pass: both non-temporal
-__device__ __forceinline__ u32x4 cn_load(const uint16_t* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-}
+// G (rows of any alignment) is read once and the stage (16-byte rows) written
+// once per pass: both non-temporal
 __device__ __forceinline__ void cn_store(uint16_t* p, u32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
@@ -70,12 +68,12 @@ __global__ __launch_bounds__(kThreads) void colnorm_partial_kernel(const DevMat*
     const int64_t ld = d.ld_grad;
     uint16_t* __restrict__ sbase = st ? d.acc1 + c0 : nullptr;
     const int64_t sld = d.ld_acc1;
-    if (d.vec && c0 + 8 <= d.m) {
+    if (c0 + 8 <= d.m) {
       int64_t i = r0 + wave;
       for (; i + 4 * (kCnBatch - 1) < r1; i += 4 * kCnBatch) {
         u32x4 v[kCnBatch];
 #pragma unroll
-        for (int b = 0; b < kCnBatch; ++b) v[b] = cn_load(base + (i + 4 * b) * ld);
+        for (int b = 0; b < kCnBatch; ++b) v[b] = load8_bf16(base + (i + 4 * b) * ld);
         if (st) {
 #pragma unroll
           for (int b = 0; b < kCnBatch; ++b) cn_store(sbase + (i + 4 * b) * sld, v[b]);
@@ -84,7 +82,7 @@ __global__ __launch_bounds__(kThreads) void colnorm_partial_kernel(const DevMat*
         for (int b = 0; b < kCnBatch; ++b) accum8(acc, v[b]);
       }
       for (; i < r1; i += 4) {
-        const u32x4 v = cn_load(base + i * ld);
+        const u32x4 v = load8_bf16(base + i * ld);
         if (st) cn_store(sbase + i * sld, v);
         accum8(acc, v);
       }

@@ -39,6 +39,11 @@
 // are loaded and staged in LDS like G, and the pack lanes take their
 // previous values from there instead of from A.
 //
+// PH: the interval's phase as a compile-time constant (1: its first step, 2: its
+// second, where the stage may be read), or 0 to take it from `first` (later
+// steps, and Zen-auto, which has no stage): each phase holds only the registers
+// and the LDS it needs.
+//
 // STATS (Zen-auto; with HAND on an end the caller
 // forces, the sums before the scale): each lane also sums, in fp64 and
 // in row order, the squares of its selected columns' gradient and of its
@@ -91,14 +96,12 @@ __device__ __forceinline__ void widen_group(u32x4 v, float (&f)[8]) {
     f[x] = widen_bf16(static_cast<uint16_t>(w[x >> 1] >> (16 * (x & 1))));
 }
 
-// Row b of a batch, 8 columns at byte offset vo: one 16-byte load, or the
-// ragged tail of a tile element by element (zeros past the tile).
-template <int AUX>
-__device__ __forceinline__ u32x4 load_group(rsrc_t r, uint32_t vo, uint32_t so, int32_t cols) {
-  if (cols >= 8) return buf_b128<AUX>(r, vo, so);
+// The first `cols` (at most 8) columns at p: one 16-byte load, or the ragged
+// tail of a tile element by element (zeros past the tile).
+__device__ __forceinline__ u32x4 load_group(const uint16_t* __restrict__ p, int32_t cols) {
+  if (cols >= 8) return load8_bf16(p);
   uint32_t w[4] = {0u, 0u, 0u, 0u};
-  for (int x = 0; x < cols; ++x)
-    w[x >> 1] |= static_cast<uint32_t>(buf_u16<AUX>(r, vo + 2 * x, so)) << (16 * (x & 1));
+  for (int x = 0; x < cols; ++x) w[x >> 1] |= static_cast<uint32_t>(p[x]) << (16 * (x & 1));
   return u32x4{w[0], w[1], w[2], w[3]};
 }
 
@@ -114,7 +117,7 @@ __device__ __forceinline__ u32x4 as_u4(float a, float b, float c, float d) {
   return u32x4{__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
 }
 
-template <bool BATCHED, bool ADAM, bool PACK, bool HAND, bool STATS, bool A16, bool DEF>
+template <bool BATCHED, bool ADAM, bool PACK, bool HAND, bool STATS, int PH, bool DEF>
 __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __restrict__ mats,
                                                              const int64_t* __restrict__ off,
                                                              int32_t nmats, DevMat one, AdamK c,
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
                                                              HistTable hist,
                                                              const ZenState* __restrict__ zst) {
   static_assert(!STATS || PACK, "statistics of the packing pass");
-  static_assert(!DEF || (BATCHED && !ADAM && !PACK && !HAND && !STATS && !A16),
+  static_assert(!DEF || (BATCHED && !ADAM && !PACK && !HAND && !STATS && PH == 0),
                 "the deferred hand-over pass");
   // Zen-auto with the interval driven on the device (steps in place):
   // overwrite after an ended interval, else accumulate; HAND (an end the
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
     if constexpr (HAND) scale = 1.0f / static_cast<float>(first);
   }
   __shared__ __attribute__((aligned(16))) uint16_t sg[kRvBatch][kRvMaxCols];
-  __shared__ __attribute__((aligned(16))) uint16_t sa[A16 ? kRvBatch : 1][A16 ? kRvMaxCols : 8];
+  __shared__ __attribute__((aligned(16))) uint16_t sa[PH == 2 ? kRvBatch : 1][PH == 2 ? kRvMaxCols : 8];
   __shared__ __attribute__((aligned(16))) float sd[HAND ? kRvBatch : 1][HAND ? kRvMaxCols : 4];
 
   int64_t local;
@@ -213,19 +216,21 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   const int64_t i0 = rblk * d.rv_rows;
   const int64_t i1 = min(i0 + static_cast<int64_t>(d.rv_rows), d.n);
   const int32_t rows = static_cast<int32_t>(i1 - i0);
-  const rsrc_t rG = rows_rsrc(d.grad, i0, i1, d.ld_grad, d.m);
-  const uint32_t sG = static_cast<uint32_t>(d.ld_grad * 2);
+  const uint16_t* __restrict__ gbase = d.grad + i0 * d.ld_grad + c0;
+  const uint16_t* __restrict__ sbase = nullptr;
   rsrc_t rA = rsrc_t(), rP = rsrc_t(), rM = rsrc_t(), rV = rsrc_t(), rW = rsrc_t(), rD = rsrc_t();
   uint32_t sA = 0, sS = 0, sW = 0, sD = 0;
   rsrc_t rT = rsrc_t();
   uint32_t sT = 0;
-  const bool a16 = A16 && PACK && d.acc1 != nullptr;
-  const bool put16 = a16 && first == 1 && !HAND;  // store G rows to the stage
-  const bool get16 = a16 && first == 2;           // read the stage rows
+  if constexpr (PH != 0) first = PH;
+  const bool a16 = (PH == 2 || (PH == 1 && !HAND)) && PACK && d.acc1 != nullptr;
+  const bool put16 = PH == 1 && a16;  // store G rows to the stage
+  const bool get16 = PH == 2 && a16;  // read the stage rows
   if constexpr (PACK) {
     rA = rows_rsrc(d.acc, i0, i1, d.ld_acc, d.m - d.k);
     sA = static_cast<uint32_t>(d.ld_acc * 4);
     if (a16) {
+      sbase = d.acc1 + i0 * d.ld_acc1 + c0;
       rT = rows_rsrc(d.acc1, i0, i1, d.ld_acc1, d.m);
       sT = static_cast<uint32_t>(d.ld_acc1 * 2);
     }
@@ -273,24 +278,8 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
       gv[p] = u32x4{0u, 0u, 0u, 0u};
       av[p] = u32x4{0u, 0u, 0u, 0u};
       if (b < nb && g8 < width) {
-        const uint32_t so = static_cast<uint32_t>(i + b) * sG;
-        const uint32_t vo = static_cast<uint32_t>((c0 + g8) * 2);
-        const uint32_t to = static_cast<uint32_t>(i + b) * sT;
-        if (g8 + 8 <= width) {
-          gv[p] = buf_b128<kStream>(rG, vo, so);
-          if (get16) av[p] = buf_b128<kStream>(rT, vo, to);
-        } else {
-          uint32_t w[4] = {0u, 0u, 0u, 0u}, x4[4] = {0u, 0u, 0u, 0u};
-          for (int x = 0; g8 + x < width; ++x) {
-            w[x >> 1] |= static_cast<uint32_t>(buf_u16<kStream>(rG, vo + 2 * x, so))
-                         << (16 * (x & 1));
-            if (get16)
-              x4[x >> 1] |= static_cast<uint32_t>(buf_u16<kStream>(rT, vo + 2 * x, to))
-                            << (16 * (x & 1));
-          }
-          gv[p] = u32x4{w[0], w[1], w[2], w[3]};
-          av[p] = u32x4{x4[0], x4[1], x4[2], x4[3]};
-        }
+        gv[p] = load_group(gbase + (i + b) * d.ld_grad + g8, width - g8);
+        if (get16) av[p] = load_group(sbase + (i + b) * d.ld_acc1 + g8, width - g8);
       }
     }
     if (put16) {
@@ -316,7 +305,6 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
     if constexpr (DEF) {
       // the hand-over of the lane's 8 columns in rows 2p + h of the batch
       const int32_t cols = width - g8;
-      const uint32_t vo = static_cast<uint32_t>((c0 + g8) * 2);
       float a[kRvBatch / 2][8];
       for (int32_t s0 = 0; s0 < hist.n; s0 += kDefBatch) {
         u32x4 ev[kDefBatch][kRvBatch / 2];
@@ -325,14 +313,13 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
           const int32_t st = s0 + e;
           if (st < hist.n) {
             const auto& hd = const_table(hist.mats[st])[q];
-            const rsrc_t rE = rows_rsrc(hd.grad, i0, i1, hd.ld_grad, d.m);
-            const uint32_t sE = static_cast<uint32_t>(hd.ld_grad * 2);
+            const uint16_t* __restrict__ ebase = hd.grad + i0 * hd.ld_grad + c0;
 #pragma unroll
             for (int p = 0; p < kRvBatch / 2; ++p) {
               const int b = 2 * p + h;
               ev[e][p] = u32x4{0u, 0u, 0u, 0u};
               if (b < nb && cols > 0)
-                ev[e][p] = load_group<kStream>(rE, vo, static_cast<uint32_t>(i + b) * sE, cols);
+                ev[e][p] = load_group(ebase + (i + b) * hd.ld_grad + g8, cols);
             }
           }
         }
@@ -543,33 +530,34 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   }
 }
 
-template <bool ADAM, bool PACK, bool HAND, bool STATS, bool A16>
+template <bool ADAM, bool PACK, bool HAND, bool STATS, int PH>
 void launch_rv_a(const Table& t, const DevMat& one, dim3 grid, const AdamK& c, int32_t first,
                  float scale, hipStream_t s, double* zs, const ZenState* zst = nullptr) {
   const HistTable none{};
   if (t.mats != nullptr)
-    hipLaunchKernelGGL((rv_update_kernel<true, ADAM, PACK, HAND, STATS, A16, false>), grid,
+    hipLaunchKernelGGL((rv_update_kernel<true, ADAM, PACK, HAND, STATS, PH, false>), grid,
                        dim3(kThreads), 0, s, t.mats, t.off, t.nmats, one, c, first, scale, zs,
                        none, zst);
   else
-    hipLaunchKernelGGL((rv_update_kernel<false, ADAM, PACK, HAND, STATS, A16, false>), grid,
+    hipLaunchKernelGGL((rv_update_kernel<false, ADAM, PACK, HAND, STATS, PH, false>), grid,
                        dim3(kThreads), 0, s, t.mats, t.off, t.nmats, one, c, first, scale, zs,
                        none, zst);
 }
 
-// The stage's code (and its registers and LDS) only in the launches of the
-// phases that use it: an interval's first step without the hand-over, and
-// its second step.  (Zen-auto statistics never run with a row-major stage.)
 template <bool ADAM, bool PACK, bool HAND, bool STATS = false>
 void launch_rv_t(const Table& t, const DevMat& one, dim3 grid, const AdamK& c, int32_t first,
                  float scale, hipStream_t s, double* zs = nullptr, const ZenState* zst = nullptr) {
   if constexpr (PACK && !STATS) {
-    if (zst == nullptr && (first == 2 || (first == 1 && !HAND))) {
-      launch_rv_a<ADAM, PACK, HAND, STATS, true>(t, one, grid, c, first, scale, s, zs);
+    if (first == 1) {
+      launch_rv_a<ADAM, PACK, HAND, STATS, 1>(t, one, grid, c, first, scale, s, zs);
+      return;
+    }
+    if (first == 2) {
+      launch_rv_a<ADAM, PACK, HAND, STATS, 2>(t, one, grid, c, first, scale, s, zs);
       return;
     }
   }
-  launch_rv_a<ADAM, PACK, HAND, STATS, false>(t, one, grid, c, first, scale, s, zs, zst);
+  launch_rv_a<ADAM, PACK, HAND, STATS, 0>(t, one, grid, c, first, scale, s, zs, zst);
 }
 
 }  // namespace
@@ -601,9 +589,9 @@ hipError_t launch_rv_handover_deferred(const Table& t, const DevMat& one, int64_
                                        hipStream_t s) {
   (void)hipGetLastError();
   if (blocks <= 0 || t.mats == nullptr) return hipSuccess;
-  launch_rv_a<true, false, false, false, false>(t, one, dim3(static_cast<uint32_t>(blocks)), c, 0,
+  launch_rv_a<true, false, false, false, 0>(t, one, dim3(static_cast<uint32_t>(blocks)), c, 0,
                                                 1.0f, s, nullptr);
-  hipLaunchKernelGGL((rv_update_kernel<true, false, false, false, false, false, true>),
+  hipLaunchKernelGGL((rv_update_kernel<true, false, false, false, false, 0, true>),
                      dim3(static_cast<uint32_t>(blocks)), dim3(kThreads), 0, s, t.mats, t.off,
                      t.nmats, one, c, 0, scale, nullptr, h, nullptr);
   return hipGetLastError();

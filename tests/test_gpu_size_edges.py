@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle as O
-from tests._gpu import bf16_dev, f32_np, mask_np, rel_close
+from tests._gpu import bf16_dev, bits_np, f32_np, mask_np, rel_close, same_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -65,15 +65,16 @@ def test_selection_variants(m, kind):
         assert np.array_equal(got.prefix.cpu().numpy(), want.prefix), (m, kind, ratio)
 
 
-# Row-major Zen-auto: the 16-byte update with its statistics (and on a refresh
-# the packing pass with them, after the per-column Adam) against the
-# per-column update with the separate statistics pass, which buffers off the
-# 16-byte path run.  Same fp64 partials in the same order: identical bits.
-# Rows at the edges of the row batches and row blocks, columns at the edges of
-# the tiles (multiples of 64 up to 960, else of 8 up to 1000).
+# Row-major Zen-auto: the 16-byte update with its statistics, and on a refresh
+# the packing pass with them after the per-column Adam, on gradient rows that
+# are 16-byte aligned and that are not, against the channel-major kernels:
+# identical states, weights and sums, statistics up to the order of the fp64
+# sums (half an ulp of fp32 on either side).  Rows at the edges of the row
+# batches and row blocks, columns at the edges of the tiles (multiples of 64 up
+# to 960, else of 8 up to 1000).
 @pytest.mark.parametrize("n", [1, 15, 17, 129])
 @pytest.mark.parametrize("m", [8, 960, 961, 1000, 1921])
-def test_row_major_zen_paths_agree(n, m):
+def test_row_major_zen_against_channel_major(n, m):
     k = zf.k_from_ratio(0.1, m)
     dev = torch.device("cuda")
     rng = np.random.default_rng(n + 7 * m)
@@ -82,14 +83,19 @@ def test_row_major_zen_paths_agree(n, m):
     master = torch.from_numpy(rng.standard_normal((n, m)).astype(np.float32)).to(dev)
     scores = [torch.from_numpy(rng.random(m).astype(np.float32)).to(dev) for _ in range(2)]
     got = []
-    for aligned in (True, False):
+    for form in ("channel", "aligned", "unaligned"):
+        cm = form == "channel"
+        L = zf.CHANNEL_MAJOR if cm else zf.ROW_MAJOR
+
         def bf16(b):
-            return bf16_dev(b, ld=-(-m // 8) * 8) if aligned else bf16_dev(b, offset=1)
+            if cm:
+                return bf16_dev(np.ascontiguousarray(b.T))
+            return bf16_dev(b, offset=1) if form == "unaligned" else bf16_dev(b, ld=-(-m // 8) * 8)
 
         sels = [zf.topk_select(s, 0.1) for s in scores]
         w = bf16(w0)
-        acc = zf.alloc_stored(zf.ROW_MAJOR, n, m - k)
-        st = [[zf.alloc_stored(zf.ROW_MAJOR, n, k) for _ in range(3)] for _ in range(2)]
+        acc = zf.alloc_stored(L, n, m - k)
+        st = [[zf.alloc_stored(L, n, k) for _ in range(3)] for _ in range(2)]
         sq = torch.zeros(k, device=dev), torch.zeros(m - k, device=dev)
         totals = torch.zeros(zf.ZEN_TOTALS_BYTES // 8, dtype=torch.int64, device=dev)
         out = []
@@ -98,15 +104,47 @@ def test_row_major_zen_paths_agree(n, m):
                                        (zf.STATES_REMAP, 1)]):
             src = zf.StateSource(prev=sels[1 - p], prev_master=st[1 - p][0],
                                  prev_exp_avg=st[1 - p][1], prev_exp_avg_sq=st[1 - p][2],
-                                 init_master=master)
+                                 init_master=master.t().contiguous() if cm else master)
             plan = zf.Plan([zf.MatrixBuffers(
                 grad=bf16(g[t]), k=k, sel=sels[p], weight=w, master=st[p][0], exp_avg=st[p][1],
-                exp_avg_sq=st[p][2], acc=acc, src=src, sel_sq=sq[0], acc_sq=sq[1])])
+                exp_avg_sq=st[p][2], acc=acc, src=src, sel_sq=sq[0], acc_sq=sq[1], layout=L)])
             plan.update_zen(zf.AdamHparams(lr=1e-3), t + 1, mode, 1 + (t == 1), 4, 1.0, totals)
             torch.cuda.synchronize()
-            out += [x.clone() for x in (w, acc, *st[p], *sq, totals)]
+            bits = [bits_np(w)] + [f32_np(x) for x in (acc, *st[p])]
+            out.append(([x.T if cm else x for x in bits], [f32_np(x) for x in sq]))
             plan.close()
         got.append(out)
-    for i, (a, b) in enumerate(zip(*got)):
-        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a,
-                           b.view(torch.int16) if b.dtype == torch.bfloat16 else b), (n, m, i)
+    for form, other in zip(("aligned", "unaligned"), got[1:]):
+        for t, ((bits, stats), (bits2, stats2)) in enumerate(zip(got[0], other)):
+            for i, (a, b) in enumerate(zip(bits, bits2)):
+                assert same_bits(a, b), (form, n, m, t, i)
+            for a, b in zip(stats, stats2):
+                assert rel_close(b, a, 2.0 ** -22)[0], (form, n, m, t)
+
+
+# Row-major plain steps on gradient rows of an odd number of elements: the
+# 16-byte kernel (all phases, with and without the bf16 stage, the deferred
+# hand-over) against the oracle, bit for bit, through the runner.
+@pytest.mark.parametrize("shape", [(33, 1003), (130, 965), (7, 9), (64, 2049)])
+@pytest.mark.parametrize("how", ["stage", "plain", "deferred"])
+def test_row_major_odd_rows_runner(shape, how):
+    n, m = shape
+    rng = np.random.default_rng(n + m)
+    R, S = 8, 4
+    bits = [gbits(n, m, 100 * n + m + t) for t in range(4)]
+    w = O.bf16_round((0.02 * rng.standard_normal((n, m))).astype(np.float32))
+    hp = zf.AdamHparams(lr=1e-3, weight_decay=0.01)
+    wd = bf16_dev(w)
+    r = zf.SelectiveUpdateRunner([shape], 0.1, hp, R, S, [[bf16_dev(b)] for b in bits], [wd],
+                                 first_step_stage=how == "stage", deferred_pack=how == "deferred")
+    orc = O.MatrixOracle(O.widen(w), w, 0.1, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay,
+                         R, S)
+    for t in range(1, 9):
+        kind = r.step()
+        want = orc.step(bits[(t - 1) % 4])
+        torch.cuda.synchronize()
+        assert np.array_equal(bits_np(wd), orc.W), t
+        for got, exp in zip(r.state[0], (orc.P, orc.M, orc.V)):
+            assert same_bits(f32_np(got), exp), t
+        if kind.interval_end:
+            assert same_bits(f32_np(r.unpacked[0]), want["unpacked"]), t
