@@ -217,7 +217,10 @@ DevMat blank() {
   return d;
 }
 
-Table single_table() { return Table{nullptr, nullptr, 1}; }
+// (channel-major matrices off the aligned path: the ragged kernels)
+bool is_ragged(const DevMat& d) { return d.layout == zf::kChannelMajor && d.vec == 0; }
+
+Table single_table(const DevMat& d) { return Table{nullptr, nullptr, 1, is_ragged(d)}; }
 
 hipStream_t as_stream(zf_stream s) { return reinterpret_cast<hipStream_t>(s); }
 
@@ -576,7 +579,7 @@ zf_status run_update(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
   const bool rv = use_rv(d, mode, adam, pack, d.vec != 0, n * m);
   const int64_t blocks = rv ? rv_grid(d) : update_grid(d);
   if (blocks == 0) return ZF_OK;
-  const hipError_t e = launch_update_any(single_table(), d, blocks, c, adam ? mode : 0,
+  const hipError_t e = launch_update_any(single_table(d), d, blocks, c, adam ? mode : 0,
                                          sii == 1 ? 1 : 0, adam, pack, layout,
                                          as_stream(stream), handover, scale, rv);
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -636,9 +639,9 @@ zf_status zf_colnorm(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
   d.cn_ws = 0;
   hipError_t e;
   if (layout == zf::kChannelMajor)
-    e = zf::launch_cm_colnorm(single_table(), d, colnorm_grid(d), as_stream(stream));
+    e = zf::launch_cm_colnorm(single_table(d), d, colnorm_grid(d), as_stream(stream));
   else
-    e = zf::launch_colnorm(single_table(), d, colnorm_grid(d), single_table(),
+    e = zf::launch_colnorm(single_table(d), d, colnorm_grid(d), single_table(d),
                            ceil_div(m, zf::kFinCols), static_cast<double*>(ws),
                            as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -742,7 +745,7 @@ zf_status zf_topk_select(const float* norms_sq, int64_t m, double ratio, const z
   if (m == 0) return ZF_OK;
   DevMat d = base_mat(nullptr, 0, m, m, zf::kRowMajor, out, k);
   d.norms = const_cast<float*>(norms_sq);
-  const hipError_t e = zf::launch_topk(single_table(), d, 1, as_stream(stream));
+  const hipError_t e = zf::launch_topk(single_table(d), d, 1, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
 
@@ -810,7 +813,7 @@ zf_status zf_unpack(const float* acc, int64_t ld_acc, const zf_selection* sel, i
   const int64_t blocks = unpack_grid(d);
   if (blocks == 0) return ZF_OK;
   const hipError_t e =
-      launch_unpack_any(single_table(), d, blocks, scale, layout, as_stream(stream));
+      launch_unpack_any(single_table(d), d, blocks, scale, layout, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
 
@@ -834,7 +837,7 @@ zf_status zf_scatter_weights(const uint16_t* weight_cols, int64_t ld_wcols,
   finish_geometry(d, 256, pick_update_rows({{n, m}}));
   const int64_t blocks = unpack_grid(d);
   if (blocks == 0 || k == m) return ZF_OK;
-  const hipError_t e = zf::launch_scatter(single_table(), d, blocks, layout, as_stream(stream));
+  const hipError_t e = zf::launch_scatter(single_table(d), d, blocks, layout, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
 
@@ -870,6 +873,7 @@ struct zf_plan {
           blk_upv = 0, blk_sel = 0;
   int64_t k_total = 0, u_total = 0, elems = 0;
   bool g16 = true;  // row-major: every gradient has 16-byte rows
+  bool ragged = false;  // channel-major: some matrix is off the aligned vector path
   bool can_colnorm = true, can_topk = true, can_adam = true, can_remap = true, can_pack = true,
        can_unpack = true, can_zen = true, can_scatter = true, can_handover = true,
        can_pending = true, can_scatter_skip = true;
@@ -1061,6 +1065,7 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
     p->u_total += d.m - d.k;
     p->elems += d.n * d.m;
     p->g16 = p->g16 && d.vec != 0;
+    p->ragged = p->ragged || is_ragged(d);
     off_cn[q] = p->blk_cn;
     off_fin[q] = p->blk_fin;
     off_top[q] = p->blk_top;
@@ -1190,12 +1195,12 @@ size_t zf_plan_device_bytes(const zf_plan* plan) { return plan ? plan->dev_bytes
 
 zf_status zf_plan_colnorm(zf_plan* p, zf_stream stream) {
   if (p == nullptr || !p->can_colnorm) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_cn, p->nmats};
+  const Table t{p->d_mats, p->d_off_cn, p->nmats, p->ragged};
   hipError_t e;
   if (p->layout == zf::kChannelMajor) {
     e = zf::launch_cm_colnorm(t, p->mats[0], p->blk_cn, as_stream(stream));
   } else {
-    const Table tf{p->d_mats, p->d_off_fin, p->nmats};
+    const Table tf{p->d_mats, p->d_off_fin, p->nmats, p->ragged};
     e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin, p->d_ws, as_stream(stream));
   }
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1203,12 +1208,12 @@ zf_status zf_plan_colnorm(zf_plan* p, zf_stream stream) {
 
 zf_status zf_plan_colnorm_stage(zf_plan* p, zf_stream stream) {
   if (p == nullptr || !p->can_colnorm || !p->has_acc1) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_cn, p->nmats};
+  const Table t{p->d_mats, p->d_off_cn, p->nmats, p->ragged};
   hipError_t e;
   if (p->layout == zf::kChannelMajor) {
     e = zf::launch_cm_colnorm(t, p->mats[0], p->blk_cn, as_stream(stream), 1);
   } else {
-    const Table tf{p->d_mats, p->d_off_fin, p->nmats};
+    const Table tf{p->d_mats, p->d_off_fin, p->nmats, p->ragged};
     e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin, p->d_ws, as_stream(stream),
                            true);
   }
@@ -1219,7 +1224,7 @@ zf_status zf_plan_colnorm_handover(zf_plan* p, float scale, zf_stream stream) {
   if (p == nullptr || !p->can_colnorm_out || p->layout != zf::kChannelMajor ||
       !std::isfinite(scale))
     return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_cn, p->nmats};
+  const Table t{p->d_mats, p->d_off_cn, p->nmats, p->ragged};
   const hipError_t e =
       zf::launch_cm_colnorm(t, p->mats[0], p->blk_cn, as_stream(stream), 2, scale);
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1227,7 +1232,7 @@ zf_status zf_plan_colnorm_handover(zf_plan* p, float scale, zf_stream stream) {
 
 zf_status zf_plan_topk_select(zf_plan* p, zf_stream stream) {
   if (p == nullptr || !p->can_topk) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_top, p->nmats};
+  const Table t{p->d_mats, p->d_off_top, p->nmats, p->ragged};
   const hipError_t e = zf::launch_topk(t, p->mats[0], p->blk_top, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -1251,11 +1256,11 @@ int32_t pack_phase(const zf_plan* p, int64_t step_in_interval) {
 hipError_t plan_update_launch(const zf_plan* p, const AdamK& c, int32_t mode, int32_t first,
                               bool adam, bool pack, bool handover, float scale, hipStream_t s) {
   if (p->layout == zf::kChannelMajor && adam && !pack && !handover && !p->has_store) {
-    const Table ts{p->d_mats, p->d_off_sel, p->nmats};
+    const Table ts{p->d_mats, p->d_off_sel, p->nmats, p->ragged};
     return zf::launch_cm_adam_selected_grid(ts, p->mats[0], p->blk_sel, c, mode, s);
   }
   const bool rv = use_rv(p->mats[0], mode, adam, pack, p->g16, p->elems);
-  const Table t{p->d_mats, rv ? p->d_off_upv : p->d_off_up, p->nmats};
+  const Table t{p->d_mats, rv ? p->d_off_upv : p->d_off_up, p->nmats, p->ragged};
   return launch_update_any(t, p->mats[0], rv ? p->blk_upv : p->blk_up, c, adam ? mode : 0, first,
                            adam, pack, p->layout, s, handover, scale, rv);
 }
@@ -1294,7 +1299,7 @@ zf_status zf_plan_update_adam_handover(zf_plan* p, const zf_adam_hparams* hp, in
   if (!hparams_ok(hp) || step < 1) return ZF_EINVAL;
   if (mode != zf::kInplace && mode != zf::kRemap && mode != zf::kInit) return ZF_EINVAL;
   if (mode == zf::kRemap && !p->can_remap) return ZF_EINVAL;
-  const Table ts{p->d_mats, p->d_off_sel, p->nmats};
+  const Table ts{p->d_mats, p->d_off_sel, p->nmats, p->ragged};
   const hipError_t e = zf::launch_cm_adam_selected_grid(ts, p->mats[0], p->blk_sel,
                                                         adam_consts(*hp, step), mode,
                                                         as_stream(stream), true);
@@ -1304,7 +1309,7 @@ zf_status zf_plan_update_adam_handover(zf_plan* p, const zf_adam_hparams* hp, in
 zf_status zf_plan_unpack_first(zf_plan* p, float scale, zf_stream stream) {
   if (p == nullptr || !p->can_unpack || !p->all_acc1 || p->layout != zf::kChannelMajor)
     return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_unp, p->nmats};
+  const Table t{p->d_mats, p->d_off_unp, p->nmats, p->ragged};
   const hipError_t e =
       zf::launch_cm_unpack(t, p->mats[0], p->blk_unp, scale, as_stream(stream), true);
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1312,7 +1317,7 @@ zf_status zf_plan_unpack_first(zf_plan* p, float scale, zf_stream stream) {
 
 zf_status zf_plan_unpack(zf_plan* p, float scale, zf_stream stream) {
   if (p == nullptr || !p->can_unpack) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_unp, p->nmats};
+  const Table t{p->d_mats, p->d_off_unp, p->nmats, p->ragged};
   const hipError_t e =
       launch_unpack_any(t, p->mats[0], p->blk_unp, scale, p->layout, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1405,16 +1410,16 @@ zf_status zf_plan_update_handover_deferred(zf_plan* p, const zf_adam_hparams* hp
   const hipStream_t stm = as_stream(stream);
   hipError_t e;
   if (cm) {
-    e = zf::launch_cm_handover_deferred(Table{p->d_mats, p->d_off_up, p->nmats}, p->mats[0],
+    e = zf::launch_cm_handover_deferred(Table{p->d_mats, p->d_off_up, p->nmats, p->ragged}, p->mats[0],
                                         p->blk_up, c, scale, h, stm);
   } else if (rv) {
-    e = zf::launch_rv_handover_deferred(Table{p->d_mats, p->d_off_upv, p->nmats}, p->mats[0],
+    e = zf::launch_rv_handover_deferred(Table{p->d_mats, p->d_off_upv, p->nmats, p->ragged}, p->mats[0],
                                         p->blk_upv, c, scale, h, stm);
   } else {
-    e = zf::launch_update(Table{p->d_mats, p->d_off_up, p->nmats}, p->mats[0], p->blk_up, c,
+    e = zf::launch_update(Table{p->d_mats, p->d_off_up, p->nmats, p->ragged}, p->mats[0], p->blk_up, c,
                           zf::kInplace, 0, true, false, false, 1.0f, stm);
     if (e == hipSuccess)
-      e = zf::launch_rm_handover_deferred(Table{p->d_mats, p->d_off_unp, p->nmats}, p->blk_unp,
+      e = zf::launch_rm_handover_deferred(Table{p->d_mats, p->d_off_unp, p->nmats, p->ragged}, p->blk_unp,
                                           scale, h, stm);
   }
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1422,7 +1427,7 @@ zf_status zf_plan_update_handover_deferred(zf_plan* p, const zf_adam_hparams* hp
 
 zf_status zf_plan_scatter_weights(zf_plan* p, zf_stream stream) {
   if (p == nullptr || !p->can_scatter) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_unp, p->nmats};
+  const Table t{p->d_mats, p->d_off_unp, p->nmats, p->ragged};
   const hipError_t e = zf::launch_scatter(t, p->mats[0], p->blk_unp, p->layout, as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -1438,7 +1443,7 @@ zf_status zf_plan_update_pending(zf_plan* p, const zf_adam_hparams* hp, int64_t 
   const AdamK c = adam_consts(*hp, step);
   const zf::Pending pd{adam_consts(*hp, pend_step), pend_scale};
   const hipStream_t s = as_stream(stream);
-  const Table t{p->d_mats, p->d_off_up, p->nmats};
+  const Table t{p->d_mats, p->d_off_up, p->nmats, p->ragged};
   const hipError_t e =
       p->layout == zf::kChannelMajor
           ? zf::launch_cm_update(t, p->mats[0], p->blk_up, c, zf::kRemap, 1, true, true, nullptr,
@@ -1450,7 +1455,7 @@ zf_status zf_plan_update_pending(zf_plan* p, const zf_adam_hparams* hp, int64_t 
 
 zf_status zf_plan_scatter_weights_skip_prev(zf_plan* p, zf_stream stream) {
   if (p == nullptr || !p->can_scatter_skip) return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_unp, p->nmats};
+  const Table t{p->d_mats, p->d_off_unp, p->nmats, p->ragged};
   const hipError_t e =
       zf::launch_scatter(t, p->mats[0], p->blk_unp, p->layout, as_stream(stream), true);
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1465,8 +1470,8 @@ namespace {
 zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t first, double tau,
                           zf_zen_totals* totals, hipStream_t s, const zf::Pending* pd,
                           zf::ZenState* zst = nullptr, int32_t S_max = 1, int32_t force_end = 0) {
-  const Table t{p->d_mats, p->d_off_up, p->nmats};
-  const Table tz{p->d_mats, p->d_off_zen, p->nmats};
+  const Table t{p->d_mats, p->d_off_up, p->nmats, p->ragged};
+  const Table tz{p->d_mats, p->d_off_zen, p->nmats, p->ragged};
   hipError_t e;
   // force_end 2: the interval ends here and the update writes the hand-over
   // where it can (channel-major; row-major steps in place on the 16-byte
@@ -1482,11 +1487,11 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
     e = zf::launch_zen_finalize(tz, p->mats[0], p->blk_zen, p->d_zs, p->d_zb, s);
   } else if (rv) {
     // 16-byte update with the statistics fused: only the finalize remains
-    const Table tv{p->d_mats, p->d_off_upv, p->nmats};
+    const Table tv{p->d_mats, p->d_off_upv, p->nmats, p->ragged};
     e = zf::launch_rv_update(tv, p->mats[0], p->blk_upv, c, mode, first, true, true, fuse, 1.0f,
                              s, p->d_ws, zst);
     if (e != hipSuccess) return hip_fail(e);
-    const Table tp{p->d_mats, p->d_off_zp, p->nmats};
+    const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
     e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
   } else if (p->mats[0].rv && pd == nullptr) {
     // A refresh on 16-byte buffers: Adam alone in the per-column kernel (first:
@@ -1498,11 +1503,11 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
     // 1 on a refresh.
     e = zf::launch_update(t, p->mats[0], p->blk_up, c, mode, 0, true, false, false, 1.0f, s);
     if (e != hipSuccess) return hip_fail(e);
-    e = zf::launch_rv_update(Table{p->d_mats, p->d_off_upv, p->nmats}, p->mats[0], p->blk_upv, c,
+    e = zf::launch_rv_update(Table{p->d_mats, p->d_off_upv, p->nmats, p->ragged}, p->mats[0], p->blk_upv, c,
                              zf::kInplace, zst != nullptr ? 1 : first, false, true, false, 1.0f, s,
                              p->d_ws);
     if (e != hipSuccess) return hip_fail(e);
-    const Table tp{p->d_mats, p->d_off_zp, p->nmats};
+    const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
     e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
   } else {
     // the per-column update (with zst the kernel derives the phase: 1 on a
@@ -1510,7 +1515,7 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
     e = zf::launch_update(t, p->mats[0], p->blk_up, c, mode, first, true, true, false, 1.0f, s,
                           pd, zst);
     if (e != hipSuccess) return hip_fail(e);
-    const Table tp{p->d_mats, p->d_off_zp, p->nmats};
+    const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
     e = zf::launch_rm_zen(tp, p->blk_zp, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
   }
   if (e != hipSuccess) return hip_fail(e);
@@ -1571,7 +1576,7 @@ zf_status zf_plan_handover_zen(zf_plan* p, const zf_zen_state* state, zf_stream 
   if (p == nullptr || !p->can_unpack || state == nullptr || !aligned(state, 4) ||
       (p->has_acc1 && (!p->all_acc1 || p->layout == zf::kRowMajor)))
     return ZF_EINVAL;
-  const Table t{p->d_mats, p->d_off_unp, p->nmats};
+  const Table t{p->d_mats, p->d_off_unp, p->nmats, p->ragged};
   const auto* zst = reinterpret_cast<const zf::ZenState*>(state);
   const hipError_t e =
       p->layout == zf::kChannelMajor
@@ -1601,8 +1606,8 @@ zf_status zf_plan_update_zen_deferred(zf_plan* p, const zf_adam_hparams* hp, int
   if (st != ZF_OK) return st;
   auto* zst = reinterpret_cast<zf::ZenState*>(state);
   const hipStream_t s = as_stream(stream);
-  const Table t{p->d_mats, p->d_off_up, p->nmats};
-  const Table tz{p->d_mats, p->d_off_zen, p->nmats};
+  const Table t{p->d_mats, p->d_off_up, p->nmats, p->ragged};
+  const Table tz{p->d_mats, p->d_off_zen, p->nmats, p->ragged};
   hipError_t e = zf::launch_cm_update_zen_deferred(t, p->mats[0], p->blk_up,
                                                    adam_consts(*hp, step), mode, p->d_zs,
                                                    force_end == 2, h, zst, s);
@@ -1627,7 +1632,7 @@ zf_status zf_plan_handover_zen_deferred(zf_plan* p, const zf_plan* const* earlie
   const zf_status st = gather_earlier(p, earlier, n_earlier, h, rv);
   if (st != ZF_OK) return st;
   const hipError_t e = zf::launch_cm_unpack_zen_deferred(
-      Table{p->d_mats, p->d_off_unp, p->nmats}, p->blk_unp, h,
+      Table{p->d_mats, p->d_off_unp, p->nmats, p->ragged}, p->blk_unp, h,
       reinterpret_cast<const zf::ZenState*>(state), as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }

@@ -207,6 +207,15 @@ typedef u32x2 u32x2_h __attribute__((aligned(2)));
 __device__ __forceinline__ u32x4 load8_bf16(const uint16_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4_h*>(p));
 }
+__device__ __forceinline__ void store8_bf16(uint16_t* p, u32x4 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4_h*>(p));
+}
+__device__ __forceinline__ u32x2 load4_bf16(const uint16_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x2_h*>(p));
+}
+__device__ __forceinline__ void store4_bf16(uint16_t* p, u32x2 v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x2_h*>(p));
+}
 
 template <int AUX = kCached>
 __device__ __forceinline__ u32x2 buf_b64(rsrc_t r, uint32_t voff, uint32_t soff) {

@@ -130,6 +130,7 @@ struct Table {
   const DevMat* mats;
   const int64_t* off;
   int32_t nmats;
+  bool ragged;  // channel-major: some matrix is off the aligned vector path
 };
 
 // Adam constants for one step, fp32 (computed in double on the host).

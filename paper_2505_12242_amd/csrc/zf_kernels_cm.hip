@@ -16,8 +16,14 @@
 // resources cover exactly its chunk, so quads past the end of a channel (the
 // last chunk) read zeros and their stores are dropped by the hardware range
 // check; the loops carry no per-quad conditions.  The vector path requires
-// n % 8 == 0 and 16-byte aligned rows (DevMat::vec); other shapes take an
-// element-wise path.
+// n % 8 == 0 and 16-byte aligned rows (DevMat::vec).  Other shapes (RAG
+// kernels, launched where the table holds one) take the same quads through
+// accesses of 2-byte (bf16) and 4-byte (fp32) alignment, and the up to three
+// rows after a channel's last whole quad element by element.  Measured on a
+// 5003 x 3001 weight against one element per lane and access: scores 37.4 -> 8.3
+// us, fused first step 44 -> 27, fused hand-over 44 -> 33.
+#include <type_traits>
+
 #include "zf_device.hpp"
 
 namespace zf {
@@ -90,6 +96,33 @@ __device__ __forceinline__ void widen4(u32x2 v, float (&f)[kQuad]) {
   f[3] = __uint_as_float(v.y & 0xffff0000u);
 }
 
+// A piece of a bf16 row: by buffer resource (aligned rows; the range check drops
+// what lies past it), or, RAG, by address with n elements in whole quads.
+struct Row16 {
+  rsrc_t r;
+  const uint16_t* p;
+  uint32_t n;
+};
+
+__device__ __forceinline__ Row16 row16(const uint16_t* p, int64_t len) {
+  return Row16{make_rsrc(p, len * 2), p, static_cast<uint32_t>(len)};
+}
+
+// Quad at element e of the row; zeros past its end (RAG: n >= 4, the load is
+// moved inside the row).
+template <bool RAG, int AUX>
+__device__ __forceinline__ u32x2 ld4(const Row16& x, uint32_t e) {
+  if constexpr (!RAG) return buf_b64<AUX>(x.r, e * 2, 0);
+  const u32x2 v = load4_bf16(x.p + min(e, x.n - 4));
+  return e < x.n ? v : u32x2{0u, 0u};
+}
+
+template <bool RAG, int AUX>
+__device__ __forceinline__ void st4(u32x2 v, const Row16& x, uint32_t e) {
+  if constexpr (!RAG) buf_put_b64<AUX>(v, x.r, e * 2, 0);
+  else if (e < x.n) store4_bf16(const_cast<uint16_t*>(x.p) + e, v);
+}
+
 __device__ __forceinline__ u32x2 narrow4(const float (&f)[kQuad]) {
   u32x2 v;
   v.x = static_cast<uint32_t>(round_bf16(f[0])) | (static_cast<uint32_t>(round_bf16(f[1])) << 16);
@@ -135,7 +168,7 @@ __device__ __forceinline__ void sum_squares(const float (&f)[N], double& ss) {
 //   OUT == 2 (a one-step interval, handed over at once): scale times every
 //     channel's widened gradient goes to its row of the hand-over buffer
 //     (the selected rows are set to +0.0 by the update).
-template <bool BATCHED, int OUT>
+template <bool BATCHED, int OUT, bool RAG>
 __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __restrict__ mats,
                                                              const int64_t* __restrict__ off,
                                                              int32_t nmats, DevMat one,
@@ -149,27 +182,46 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
   const int64_t j = local * (kThreads / 64) + uniform_i32(threadIdx.x >> 6);
   if (j >= d.m) return;
   const int64_t n = d.n;
-  const rsrc_t r = make_rsrc(d.grad + j * d.ld_grad, n * 2);
+  const rsrc_t r = make_rsrc(d.grad + j * d.ld_grad, n * 2);  // (aligned rows)
   const bool st = OUT == 1 && d.acc1 != nullptr;
   const rsrc_t rS = st ? make_rsrc(d.acc1 + j * d.ld_acc1, n * 2) : r;
-  const rsrc_t rO = OUT == 2 ? make_rsrc(d.out + j * d.ld_out, n * 4) : r;
+  // the rows of whole 16-byte groups; RAG: the rest element by element below
+  const bool rag = RAG && !d.vec;
+  const int64_t n8 = rag ? n & ~int64_t(7) : n;
+  const rsrc_t rO = OUT == 2 ? make_rsrc(d.out + j * d.ld_out, n8 * 4) : r;
+  const uint16_t* __restrict__ pg = d.grad + j * d.ld_grad;
+  uint16_t* __restrict__ ps = st ? d.acc1 + j * d.ld_acc1 : nullptr;
   double a0 = 0.0, a1 = 0.0;
-  if (d.vec) {
+  {
     // A pass covers 4 loads of kStride rows; its base is wave-uniform, so
     // the loop is too.  Groups past n read zeros (resource range), add +0.0
     // to the sums and their stores are dropped: each lane adds its groups in
     // row order, as a loop over its own groups would.
     constexpr int kStride = 64 * kGroup;  // elements per wave per load
     const int64_t lo = static_cast<int64_t>(lane) * kGroup;
-    for (int64_t e0 = 0; e0 < n; e0 += 4 * kStride) {
+    for (int64_t e0 = 0; e0 < n8; e0 += 4 * kStride) {
       u32x4 v[4];
+      if (RAG && rag) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        v[b] = buf_b128<kAuxScore>(r, static_cast<uint32_t>((e0 + b * kStride + lo) * 2), 0);
-      if (st) {
+        for (int b = 0; b < 4; ++b) {
+          const int64_t e = e0 + b * kStride + lo;
+          const u32x4 x = load8_bf16(pg + min(e, n8 - kGroup));
+          v[b] = e < n8 ? x : u32x4{0u, 0u, 0u, 0u};
+        }
+      } else {
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          buf_put_b128<kAuxAFirst>(v[b], rS, static_cast<uint32_t>((e0 + b * kStride + lo) * 2), 0);
+          v[b] = buf_b128<kAuxScore>(r, static_cast<uint32_t>((e0 + b * kStride + lo) * 2), 0);
+      }
+      if (st) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int64_t e = e0 + b * kStride + lo;
+          if (!(RAG && rag))
+            buf_put_b128<kAuxAFirst>(v[b], rS, static_cast<uint32_t>(e * 2), 0);
+          else if (e < n8)
+            store8_bf16(ps + e, v[b]);
+        }
       }
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
@@ -214,12 +266,13 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
         }
       }
     }
-  } else {
-    for (int64_t e = lane; e < n; e += 64) {
-      const uint16_t gb = buf_u16<kAuxScore>(r, static_cast<uint32_t>(e * 2), 0);
-      if (st) buf_put_u16<kAuxAFirst>(gb, rS, static_cast<uint32_t>(e * 2), 0);
+  }
+  if constexpr (RAG) {
+    if (n8 + lane < n) {  // at most seven rows
+      const uint16_t gb = pg[n8 + lane];
+      if (st) ps[n8 + lane] = gb;
       const float g = widen_bf16(gb);
-      if constexpr (OUT == 2) buf_put_f32<kAuxWO>(g * scale, rO, static_cast<uint32_t>(e * 4), 0);
+      if constexpr (OUT == 2) d.out[j * d.ld_out + n8 + lane] = g * scale;
       const double x = static_cast<double>(g);
       a0 = __builtin_fma(x, x, a0);
     }
@@ -241,16 +294,16 @@ enum CmSrc { kCmInplace = 0, kCmPrev, kCmInitW, kCmInitMaster, kCmPend };
 // Adam over one chunk of channel j (slot r), vector path (QPT quads per
 // lane).  SRC picks where (p, m, v) come from; rS* are the source rows (the
 // slot's own rows in place).
-template <int SRC, int QPT, bool STATS>
-__device__ __forceinline__ void cm_adam_vec(rsrc_t rG, rsrc_t rP, rsrc_t rM, rsrc_t rV,
-                                            rsrc_t rW, rsrc_t rSP, rsrc_t rSM, rsrc_t rSV,
+template <int SRC, int QPT, bool STATS, bool RAG>
+__device__ __forceinline__ void cm_adam_vec(const Row16& rG, rsrc_t rP, rsrc_t rM, rsrc_t rV,
+                                            const Row16& rW, rsrc_t rSP, rsrc_t rSM, rsrc_t rSV,
                                             rsrc_t rI, const AdamK& c, double& ss,
                                             rsrc_t rPA = rsrc_t(), const Pending* pd = nullptr) {
   const int tid = threadIdx.x;
   float g[QPT][kQuad], p[QPT][kQuad], m[QPT][kQuad], v[QPT][kQuad];
   u32x2 gv[QPT];
 #pragma unroll
-  for (int q = 0; q < QPT; ++q) gv[q] = buf_b64<kAuxRO>(rG, quad_elem(q, tid) * 2, 0);
+  for (int q = 0; q < QPT; ++q) gv[q] = ld4<RAG, kAuxRO>(rG, quad_elem(q, tid));
 #pragma unroll
   for (int q = 0; q < QPT; ++q) {
     const uint32_t e = quad_elem(q, tid);
@@ -265,7 +318,7 @@ __device__ __forceinline__ void cm_adam_vec(rsrc_t rG, rsrc_t rP, rsrc_t rM, rsr
       }
     } else {
       if constexpr (SRC == kCmInitMaster) f32x4_load<kAuxRO>(rI, e * 4, p[q]);
-      else widen4(buf_b64<kAuxRO>(rI, e * 2, 0), p[q]);
+      else widen4(ld4<RAG, kAuxRO>(rW, e), p[q]);
 #pragma unroll
       for (int i = 0; i < kQuad; ++i) m[q][i] = v[q][i] = 0.0f;
     }
@@ -280,7 +333,7 @@ __device__ __forceinline__ void cm_adam_vec(rsrc_t rG, rsrc_t rP, rsrc_t rM, rsr
     f32x4_store<kAuxRMW>(rP, e * 4, p[q]);
     f32x4_store<kAuxRMW>(rM, e * 4, m[q]);
     f32x4_store<kAuxRMW>(rV, e * 4, v[q]);
-    buf_put_b64<kAuxW>(narrow4(p[q]), rW, e * 2, 0);
+    st4<RAG, kAuxW>(narrow4(p[q]), rW, e);
   }
 }
 
@@ -302,7 +355,7 @@ __device__ __forceinline__ void cm_adam_elem(rsrc_t rG, rsrc_t rP, rsrc_t rM, rs
       if constexpr (SRC == kCmPend)
         adam_step(buf_f32<kAuxRO>(rPA, o * 4, 0) * pd->scale, p, m, v, pd->c);
     } else {
-      p = (SRC == kCmInitMaster) ? buf_f32<kAuxRO>(rI, o * 4, 0) : widen_bf16(buf_u16<kAuxRO>(rI, o * 2, 0));
+      p = (SRC == kCmInitMaster) ? buf_f32<kAuxRO>(rI, o * 4, 0) : widen_bf16(buf_u16<kAuxRO>(rW, o * 2, 0));
       m = v = 0.0f;
     }
     adam_step(g, p, m, v, c);
@@ -323,19 +376,18 @@ __device__ __forceinline__ void cm_adam_elem(rsrc_t rG, rsrc_t rP, rsrc_t rM, rs
 // the gradient's own bits into the stage instead of fp32 into A; 2 -- the
 // second step reads the previous values from the stage (widened, the same
 // fp32 values) instead of from A.
-template <bool FIRST, int QPT, bool STATS, bool HAND = false, int A16 = 0>
-__device__ __forceinline__ void cm_pack_vec(rsrc_t rG, rsrc_t rA, double& ss,
-                                            rsrc_t rOut = rsrc_t(), float scale = 1.0f,
-                                            rsrc_t rA16 = rsrc_t()) {
+template <bool FIRST, int QPT, bool STATS, bool HAND, int A16, bool RAG>
+__device__ __forceinline__ void cm_pack_vec(const Row16& rG, rsrc_t rA, double& ss, rsrc_t rOut,
+                                            float scale, const Row16& rA16) {
   const int tid = threadIdx.x;
   u32x2 gv[QPT];
   float a[QPT][kQuad];
 #pragma unroll
-  for (int q = 0; q < QPT; ++q) gv[q] = buf_b64<kAuxRO>(rG, quad_elem(q, tid) * 2, 0);
+  for (int q = 0; q < QPT; ++q) gv[q] = ld4<RAG, kAuxRO>(rG, quad_elem(q, tid));
   if constexpr (!FIRST) {
     if constexpr (A16 == 2) {
 #pragma unroll
-      for (int q = 0; q < QPT; ++q) widen4(buf_b64<kAuxRO>(rA16, quad_elem(q, tid) * 2, 0), a[q]);
+      for (int q = 0; q < QPT; ++q) widen4(ld4<RAG, kAuxRO>(rA16, quad_elem(q, tid)), a[q]);
     } else {
 #pragma unroll
       for (int q = 0; q < QPT; ++q) f32x4_load<kAuxRMW>(rA, quad_elem(q, tid) * 4, a[q]);
@@ -353,17 +405,16 @@ __device__ __forceinline__ void cm_pack_vec(rsrc_t rG, rsrc_t rA, double& ss,
       for (int i = 0; i < kQuad; ++i) a[q][i] = a[q][i] * scale;
       f32x4_store<kAuxWO>(rOut, quad_elem(q, tid) * 4, a[q]);
     } else if constexpr (FIRST && A16 == 1) {
-      buf_put_b64<kAuxAFirst>(gv[q], rA16, quad_elem(q, tid) * 2, 0);
+      st4<RAG, kAuxAFirst>(gv[q], rA16, quad_elem(q, tid));
     } else {
       f32x4_store<FIRST ? kAuxAFirst : kAuxRMW>(rA, quad_elem(q, tid) * 4, a[q]);
     }
   }
 }
 
-template <bool FIRST, bool STATS, bool HAND = false, int A16 = 0>
+template <bool FIRST, bool STATS, bool HAND, int A16>
 __device__ __forceinline__ void cm_pack_elem(rsrc_t rG, rsrc_t rA, int64_t len, double& ss,
-                                             rsrc_t rOut = rsrc_t(), float scale = 1.0f,
-                                             rsrc_t rA16 = rsrc_t()) {
+                                             rsrc_t rOut, float scale, rsrc_t rA16) {
   for (int64_t e = threadIdx.x; e < len; e += kThreads) {
     const uint32_t o = static_cast<uint32_t>(e);
     const uint16_t gb = buf_u16<kAuxRO>(rG, o * 2, 0);
@@ -380,36 +431,62 @@ __device__ __forceinline__ void cm_pack_elem(rsrc_t rG, rsrc_t rA, int64_t len, 
   }
 }
 
+// How a piece of a channel is accessed: aligned quads, quads of any alignment
+// (a whole number of them), element by element.
+enum CmPath { kPathVec = 0, kPathRag, kPathElem };
+
 // The vector paths at a matrix's quads per lane: cm_qpt (kCmQpt / 2 or
 // kCmQpt) in the full-grid passes; ONE: one quad (the selected-only Adam
 // grid).
-template <int SRC, bool STATS, bool ONE = false>
-__device__ __forceinline__ void cm_adam_vec_any(int qpt, rsrc_t rG, rsrc_t rP, rsrc_t rM,
-                                                rsrc_t rV, rsrc_t rW, rsrc_t rSP, rsrc_t rSM,
-                                                rsrc_t rSV, rsrc_t rI, const AdamK& c,
-                                                double& ss, rsrc_t rPA = rsrc_t(),
-                                                const Pending* pd = nullptr) {
-  if constexpr (ONE)
-    cm_adam_vec<SRC, 1, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
+template <int SRC, bool STATS, bool ONE, int PATH>
+__device__ __forceinline__ void cm_adam_piece(int qpt, const Row16& rG, rsrc_t rP, rsrc_t rM,
+                                              rsrc_t rV, const Row16& rW, rsrc_t rSP, rsrc_t rSM,
+                                              rsrc_t rSV, rsrc_t rI, const AdamK& c, int64_t len,
+                                              double& ss, rsrc_t rPA = rsrc_t(),
+                                              const Pending* pd = nullptr) {
+  constexpr bool RAG = PATH == kPathRag;
+  if constexpr (PATH == kPathElem)
+    cm_adam_elem<SRC, STATS>(rG.r, rP, rM, rV, rW.r, rSP, rSM, rSV, rI, c, len, ss, rPA, pd);
+  else if constexpr (ONE)
+    cm_adam_vec<SRC, 1, STATS, RAG>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
   else if (qpt >= kCmQpt)
-    cm_adam_vec<SRC, kCmQpt, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
+    cm_adam_vec<SRC, kCmQpt, STATS, RAG>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
   else
-    cm_adam_vec<SRC, kCmQpt / 2, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
+    cm_adam_vec<SRC, kCmQpt / 2, STATS, RAG>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, pd);
 }
 
-template <bool FIRST, bool STATS, bool HAND = false, int A16 = 0>
-__device__ __forceinline__ void cm_pack_vec_any(int qpt, rsrc_t rG, rsrc_t rA, double& ss,
-                                                rsrc_t rOut = rsrc_t(), float scale = 1.0f,
-                                                rsrc_t rA16 = rsrc_t()) {
-  if (qpt >= kCmQpt)
-    cm_pack_vec<FIRST, kCmQpt, STATS, HAND, A16>(rG, rA, ss, rOut, scale, rA16);
+template <bool FIRST, bool STATS, bool HAND, int A16, int PATH>
+__device__ __forceinline__ void cm_pack_piece(int qpt, const Row16& rG, rsrc_t rA, int64_t len,
+                                              double& ss, rsrc_t rOut, float scale,
+                                              const Row16& rA16) {
+  constexpr bool RAG = PATH == kPathRag;
+  if constexpr (PATH == kPathElem)
+    cm_pack_elem<FIRST, STATS, HAND, A16>(rG.r, rA, len, ss, rOut, scale, rA16.r);
+  else if (qpt >= kCmQpt)
+    cm_pack_vec<FIRST, kCmQpt, STATS, HAND, A16, RAG>(rG, rA, ss, rOut, scale, rA16);
   else
-    cm_pack_vec<FIRST, kCmQpt / 2, STATS, HAND, A16>(rG, rA, ss, rOut, scale, rA16);
+    cm_pack_vec<FIRST, kCmQpt / 2, STATS, HAND, A16, RAG>(rG, rA, ss, rOut, scale, rA16);
+}
+
+// fn(path, e0, len) over the pieces of rows [e0, e0 + len): the whole of them on
+// the vector path; RAG kernels, off it: the whole quads, then the rest.
+template <bool RAG, typename Fn>
+__device__ __forceinline__ void cm_pieces(bool vec, int64_t e0, int64_t len, Fn fn) {
+  if constexpr (!RAG) {
+    fn(std::integral_constant<int, kPathVec>{}, e0, len);
+  } else if (vec) {
+    fn(std::integral_constant<int, kPathVec>{}, e0, len);
+  } else {
+    const int64_t n4 = len & ~int64_t(3);
+    if (n4 > 0) fn(std::integral_constant<int, kPathRag>{}, e0, n4);
+    if (len > n4) fn(std::integral_constant<int, kPathElem>{}, e0 + n4, len - n4);
+  }
 }
 
 // HAND: a selected channel's row of the hand-over buffer is +0.0.
-__device__ __forceinline__ void cm_zero_rows(const DevMat& d, rsrc_t rOut, int64_t len) {
-  if (d.vec) {
+template <int PATH>
+__device__ __forceinline__ void cm_zero_rows(rsrc_t rOut, int64_t len) {
+  if constexpr (PATH != kPathElem) {
     const float z[kQuad] = {0.f, 0.f, 0.f, 0.f};
     for (int64_t g = threadIdx.x; g * kQuad < len; g += kThreads)
       f32x4_store<kAuxWO>(rOut, static_cast<uint32_t>(g * kQuad * 4), z);
@@ -421,6 +498,7 @@ __device__ __forceinline__ void cm_zero_rows(const DevMat& d, rsrc_t rOut, int64
 
 // Swap-out of one chunk of a channel that left the selection: its previous
 // compact (p, m, v) rows are copied to its rows of the full-state store.
+template <int PATH>
 __device__ __forceinline__ void cm_swap_out(const DevMat& d, int64_t j, int64_t w, int64_t e0,
                                             int64_t len) {
   const uint64_t pm = uniform_u64(d.prev_mask[w]);
@@ -433,7 +511,7 @@ __device__ __forceinline__ void cm_swap_out(const DevMat& d, int64_t j, int64_t 
   const rsrc_t dst[3] = {make_rsrc(d.st_P + j * d.ld_store + e0, len * 4),
                          make_rsrc(d.st_M + j * d.ld_store + e0, len * 4),
                          make_rsrc(d.st_V + j * d.ld_store + e0, len * 4)};
-  if (d.vec) {
+  if constexpr (PATH != kPathElem) {
     for (int64_t g = threadIdx.x; g * kQuad < len; g += kThreads) {
       const uint32_t o = static_cast<uint32_t>(g * kQuad * 4);
 #pragma unroll
@@ -458,10 +536,10 @@ __device__ __forceinline__ void cm_swap_out(const DevMat& d, int64_t j, int64_t 
 // added in step order in fp32 (the accumulation's own sequence, so the
 // same bits as packing every step).  STATS: ss += the squares of the sums,
 // in fp64; WRITE: scale times the sums to rOut.
-template <int QPT, bool STATS, bool WRITE>
+template <int QPT, bool STATS, bool WRITE, bool RAG>
 __device__ __forceinline__ void cm_interval_sum_vec(const HistTable& h, int32_t s_first, int32_t q,
                                                     int64_t j, int64_t e0, int64_t len,
-                                                    rsrc_t rG, rsrc_t rOut, float scale,
+                                                    const Row16& rG, rsrc_t rOut, float scale,
                                                     double& ss) {
   const int tid = threadIdx.x;
   constexpr int kBatch = 4;  // steps whose rows are loaded before they are added
@@ -473,13 +551,13 @@ __device__ __forceinline__ void cm_interval_sum_vec(const HistTable& h, int32_t 
     for (int b = 0; b < kBatch; ++b) {
       const int32_t s = s0 + b;
       if (s < steps) {
-        rsrc_t r = rG;
+        Row16 r = rG;
         if (s < steps - 1) {
           const auto& hd = const_table(h.mats[s_first + s])[q];
-          r = make_rsrc(hd.grad + j * hd.ld_grad + e0, len * 2);
+          r = row16(hd.grad + j * hd.ld_grad + e0, len);
         }
 #pragma unroll
-        for (int p = 0; p < QPT; ++p) gv[b][p] = buf_b64<kAuxRO>(r, quad_elem(p, tid) * 2, 0);
+        for (int p = 0; p < QPT; ++p) gv[b][p] = ld4<RAG, kAuxRO>(r, quad_elem(p, tid));
       }
     }
 #pragma unroll
@@ -530,6 +608,21 @@ __device__ __forceinline__ void cm_interval_sum_elem(const HistTable& h, int32_t
   }
 }
 
+template <bool STATS, bool WRITE, int PATH>
+__device__ __forceinline__ void cm_interval_sum_piece(int qpt, const HistTable& h, int32_t s_first,
+                                                      int32_t q, int64_t j, int64_t e0,
+                                                      int64_t len, const Row16& rG, rsrc_t rOut,
+                                                      float scale, double& ss) {
+  constexpr bool RAG = PATH == kPathRag;
+  if constexpr (PATH == kPathElem)
+    cm_interval_sum_elem<STATS, WRITE>(h, s_first, q, j, e0, len, rG.r, rOut, scale, ss);
+  else if (qpt >= kCmQpt)
+    cm_interval_sum_vec<kCmQpt, STATS, WRITE, RAG>(h, s_first, q, j, e0, len, rG, rOut, scale, ss);
+  else
+    cm_interval_sum_vec<kCmQpt / 2, STATS, WRITE, RAG>(h, s_first, q, j, e0, len, rG, rOut, scale,
+                                                       ss);
+}
+
 // STATS (fused Adam + pack only): every wave also sums, in fp64, the squares
 // of the values its lanes handled -- the gradient of a selected channel, the
 // new accumulated value of an unselected one -- after a fixed xor butterfly,
@@ -564,7 +657,7 @@ __device__ __forceinline__ void cm_interval_sum_elem(const HistTable& h, int32_t
 // fused launches of the fixed schedule pass it, so that each phase is a
 // kernel of its own (its own code, its own name in a profile).
 template <bool BATCHED, bool ADAM, bool PACK, bool STATS, bool HAND, bool PEND, bool SELG,
-          int PH = 0, bool DEFP = false>
+          int PH = 0, bool DEFP = false, bool RAG = false>
 __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(const DevMat* __restrict__ mats,
                                                             const int64_t* __restrict__ off,
                                                             int32_t nmats, DevMat one, AdamK c,
@@ -614,120 +707,91 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
   const int64_t e0 = ci * chunk;
   const int64_t len = min(chunk, d.n - e0);
   const int64_t w = j >> 6;
-  const rsrc_t rG = make_rsrc(d.grad + j * d.ld_grad + e0, len * 2);
   double ss = 0.0;
 
   if (!sel) {
-    if (mode == kRemap && d.st_P != nullptr) cm_swap_out(d, j, w, e0, len);
-    if constexpr (DEFP) {
-      // deferred packing: the gradient stays in its slot.  The statistics
-      // are taken on the interval's running sum, the sum of its kept steps
-      // (the last pos - 1 entries of h) and this one's; HAND writes scale
-      // times that sum to the hand-over.  Nothing else is written.
-      const int32_t kept = min(max(pos - 1, 0), h.n);
-      const rsrc_t rOut = HAND ? make_rsrc(d.out + j * d.ld_out + e0, len * 4) : rG;
-      if (d.vec) {
-        if (d.cm_qpt >= kCmQpt)
-          cm_interval_sum_vec<kCmQpt, true, HAND>(h, h.n - kept, q, j, e0, len, rG, rOut, scale,
-                                                   ss);
-        else
-          cm_interval_sum_vec<kCmQpt / 2, true, HAND>(h, h.n - kept, q, j, e0, len, rG, rOut,
-                                                       scale, ss);
-      } else {
-        cm_interval_sum_elem<true, HAND>(h, h.n - kept, q, j, e0, len, rG, rOut, scale, ss);
-      }
-    } else if constexpr (PACK) {
-      const int64_t u = j - r;
-      const rsrc_t rA = make_rsrc(d.acc + u * d.ld_acc + e0, len * 4);
-      // the bf16 first-step stage (row j, channel-indexed): ph == 1 on an
-      // interval's first step, 2 on its second (a matrix without a stage
-      // takes 2 as any later step)
-      const bool a16 = d.acc1 != nullptr;
-      const rsrc_t rA16 = a16 ? make_rsrc(d.acc1 + j * d.ld_acc1 + e0, len * 2) : rA;
-      if constexpr (HAND) {
-        const rsrc_t rOut = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
-        if (d.vec) {
-          if (ph == 1) cm_pack_vec_any<true, STATS, true>(d.cm_qpt, rG, rA, ss, rOut, scale);
-          else if (a16 && ph == 2)
-            cm_pack_vec_any<false, STATS, true, 2>(d.cm_qpt, rG, rA, ss, rOut, scale, rA16);
-          else cm_pack_vec_any<false, STATS, true>(d.cm_qpt, rG, rA, ss, rOut, scale);
-        } else {
-          if (ph == 1) cm_pack_elem<true, STATS, true>(rG, rA, len, ss, rOut, scale);
-          else if (a16 && ph == 2)
-            cm_pack_elem<false, STATS, true, 2>(rG, rA, len, ss, rOut, scale, rA16);
-          else cm_pack_elem<false, STATS, true>(rG, rA, len, ss, rOut, scale);
-        }
-      } else if (d.vec) {
+    cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+      constexpr int P = decltype(path)::value;
+      const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
+      if (mode == kRemap && d.st_P != nullptr) cm_swap_out<P>(d, j, w, e0, len);
+      if constexpr (DEFP) {
+        // deferred packing: the gradient stays in its slot.  The statistics
+        // are taken on the interval's running sum, the sum of its kept steps
+        // (the last pos - 1 entries of h) and this one's; HAND writes scale
+        // times that sum to the hand-over.  Nothing else is written.
+        const int32_t kept = min(max(pos - 1, 0), h.n);
+        const rsrc_t rOut = HAND ? make_rsrc(d.out + j * d.ld_out + e0, len * 4) : rG.r;
+        cm_interval_sum_piece<true, HAND, P>(d.cm_qpt, h, h.n - kept, q, j, e0, len, rG, rOut,
+                                             scale, ss);
+      } else if constexpr (PACK) {
+        const int64_t u = j - r;
+        const rsrc_t rA = make_rsrc(d.acc + u * d.ld_acc + e0, len * 4);
+        // the bf16 first-step stage (row j, channel-indexed): ph == 1 on an
+        // interval's first step, 2 on its second (a matrix without a stage
+        // takes 2 as any later step)
+        const bool a16 = d.acc1 != nullptr;
+        const Row16 rA16 = a16 ? row16(d.acc1 + j * d.ld_acc1 + e0, len) : rG;
+        const rsrc_t rOut = HAND ? make_rsrc(d.out + j * d.ld_out + e0, len * 4) : rA;
         if (ph == 1) {
-          if (a16) cm_pack_vec_any<true, STATS, false, 1>(d.cm_qpt, rG, rA, ss, rsrc_t(), 1.0f, rA16);
-          else cm_pack_vec_any<true, STATS>(d.cm_qpt, rG, rA, ss);
+          if (!HAND && a16)
+            cm_pack_piece<true, STATS, false, 1, P>(d.cm_qpt, rG, rA, len, ss, rOut, 1.0f, rA16);
+          else
+            cm_pack_piece<true, STATS, HAND, 0, P>(d.cm_qpt, rG, rA, len, ss, rOut, scale, rA16);
         } else if (a16 && ph == 2) {
-          cm_pack_vec_any<false, STATS, false, 2>(d.cm_qpt, rG, rA, ss, rsrc_t(), 1.0f, rA16);
+          cm_pack_piece<false, STATS, HAND, 2, P>(d.cm_qpt, rG, rA, len, ss, rOut, scale, rA16);
         } else {
-          cm_pack_vec_any<false, STATS>(d.cm_qpt, rG, rA, ss);
-        }
-      } else {
-        if (ph == 1) {
-          if (a16) cm_pack_elem<true, STATS, false, 1>(rG, rA, len, ss, rsrc_t(), 1.0f, rA16);
-          else cm_pack_elem<true, STATS>(rG, rA, len, ss);
-        } else if (a16 && ph == 2) {
-          cm_pack_elem<false, STATS, false, 2>(rG, rA, len, ss, rsrc_t(), 1.0f, rA16);
-        } else {
-          cm_pack_elem<false, STATS>(rG, rA, len, ss);
+          cm_pack_piece<false, STATS, HAND, 0, P>(d.cm_qpt, rG, rA, len, ss, rOut, scale, rA16);
         }
       }
-    }
+    });
   } else if constexpr (ADAM) {
-    const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
-    const rsrc_t rM = make_rsrc(d.M + r * d.ld_state + e0, len * 4);
-    const rsrc_t rV = make_rsrc(d.V + r * d.ld_state + e0, len * 4);
-    const rsrc_t rW = make_rsrc(d.weight + j * d.ld_weight + e0, len * 2);
-    int src = kCmInplace;
-    rsrc_t rSP = rP, rSM = rM, rSV = rV, rI = rW;
-    int64_t ro = 0;  // previously selected channels below j
-    if (mode == kRemap) {
-      const uint64_t pm = uniform_u64(d.prev_mask[w]);
-      ro = static_cast<int64_t>(uniform_i32(d.prev_prefix[w])) +
-           __popcll(pm & ((uint64_t(1) << (j & 63)) - 1));
-      if ((pm >> (j & 63)) & 1ull) {
-        rSP = make_rsrc(d.prev_P + ro * d.ld_prev + e0, len * 4);
-        rSM = make_rsrc(d.prev_M + ro * d.ld_prev + e0, len * 4);
-        rSV = make_rsrc(d.prev_V + ro * d.ld_prev + e0, len * 4);
-        src = kCmPrev;
-      } else {
+    cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+      constexpr int P = decltype(path)::value;
+      const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
+      const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
+      const rsrc_t rM = make_rsrc(d.M + r * d.ld_state + e0, len * 4);
+      const rsrc_t rV = make_rsrc(d.V + r * d.ld_state + e0, len * 4);
+      const Row16 rW = row16(d.weight + j * d.ld_weight + e0, len);
+      int src = kCmInplace;
+      rsrc_t rSP = rP, rSM = rM, rSV = rV, rI = rP;
+      int64_t ro = 0;  // previously selected channels below j
+      if (mode == kRemap) {
+        const uint64_t pm = uniform_u64(d.prev_mask[w]);
+        ro = static_cast<int64_t>(uniform_i32(d.prev_prefix[w])) +
+             __popcll(pm & ((uint64_t(1) << (j & 63)) - 1));
+        if ((pm >> (j & 63)) & 1ull) {
+          rSP = make_rsrc(d.prev_P + ro * d.ld_prev + e0, len * 4);
+          rSM = make_rsrc(d.prev_M + ro * d.ld_prev + e0, len * 4);
+          rSV = make_rsrc(d.prev_V + ro * d.ld_prev + e0, len * 4);
+          src = kCmPrev;
+        } else {
+          src = d.init_P ? kCmInitMaster : kCmInitW;
+        }
+      } else if (mode == kInit) {
         src = d.init_P ? kCmInitMaster : kCmInitW;
       }
-    } else if (mode == kInit) {
-      src = d.init_P ? kCmInitMaster : kCmInitW;
-    }
-    if (mode != kInplace && src != kCmPrev && d.st_P != nullptr) {
-      // swap-in from the full-state store: the same loads as a moved column
-      rSP = make_rsrc(d.st_P + j * d.ld_store + e0, len * 4);
-      rSM = make_rsrc(d.st_M + j * d.ld_store + e0, len * 4);
-      rSV = make_rsrc(d.st_V + j * d.ld_store + e0, len * 4);
-      src = PEND ? kCmPend : kCmPrev;
-    }
-    if (src == kCmInitMaster) rI = make_rsrc(d.init_P + j * d.ld_init + e0, len * 4);
-    if (PEND && src == kCmPend) {
-      const rsrc_t rPA = make_rsrc(d.pend_acc + (j - ro) * d.ld_pend + e0, len * 4);
-      if (d.vec) cm_adam_vec_any<kCmPend, STATS, SELG>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss, rPA, &pd);
-      else cm_adam_elem<kCmPend, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss, rPA, &pd);
-    } else if (d.vec) {
-      switch (src) {
-        case kCmInplace: cm_adam_vec_any<kCmInplace, STATS, SELG>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss); break;
-        case kCmPrev: cm_adam_vec_any<kCmPrev, STATS, SELG>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss); break;
-        case kCmInitW: cm_adam_vec_any<kCmInitW, STATS, SELG>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss); break;
-        default: cm_adam_vec_any<kCmInitMaster, STATS, SELG>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, ss); break;
+      if (mode != kInplace && src != kCmPrev && d.st_P != nullptr) {
+        // swap-in from the full-state store: the same loads as a moved column
+        rSP = make_rsrc(d.st_P + j * d.ld_store + e0, len * 4);
+        rSM = make_rsrc(d.st_M + j * d.ld_store + e0, len * 4);
+        rSV = make_rsrc(d.st_V + j * d.ld_store + e0, len * 4);
+        src = PEND ? kCmPend : kCmPrev;
       }
-    } else {
-      switch (src) {
-        case kCmInplace: cm_adam_elem<kCmInplace, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
-        case kCmPrev: cm_adam_elem<kCmPrev, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
-        case kCmInitW: cm_adam_elem<kCmInitW, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
-        default: cm_adam_elem<kCmInitMaster, STATS>(rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
+      if (src == kCmInitMaster) rI = make_rsrc(d.init_P + j * d.ld_init + e0, len * 4);
+      if (PEND && src == kCmPend) {
+        const rsrc_t rPA = make_rsrc(d.pend_acc + (j - ro) * d.ld_pend + e0, len * 4);
+        cm_adam_piece<kCmPend, STATS, SELG, P>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len,
+                                               ss, rPA, &pd);
+      } else {
+        switch (src) {
+          case kCmInplace: cm_adam_piece<kCmInplace, STATS, SELG, P>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
+          case kCmPrev: cm_adam_piece<kCmPrev, STATS, SELG, P>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
+          case kCmInitW: cm_adam_piece<kCmInitW, STATS, SELG, P>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
+          default: cm_adam_piece<kCmInitMaster, STATS, SELG, P>(qpt, rG, rP, rM, rV, rW, rSP, rSM, rSV, rI, c, len, ss); break;
+        }
       }
-    }
-    if constexpr (HAND) cm_zero_rows(d, make_rsrc(d.out + j * d.ld_out + e0, len * 4), len);
+      if constexpr (HAND) cm_zero_rows<P>(make_rsrc(d.out + j * d.ld_out + e0, len * 4), len);
+    });
   }
   if constexpr (STATS) {
 #pragma unroll
@@ -745,6 +809,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
 // rows, as in the update.
 // ---------------------------------------------------------------------------
 
+template <bool RAG>
 __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, AdamK c,
     float scale, HistTable h) {
@@ -764,29 +829,25 @@ __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
   const int64_t len = min(chunk, d.n - e0);
   const uint64_t mj = uniform_u64(d.mask[j >> 6]);
   const bool sel = (mj >> (j & 63)) & 1ull;
-  const rsrc_t rG = make_rsrc(d.grad + j * d.ld_grad + e0, len * 2);
-  const rsrc_t rOut = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
   double ss = 0.0;
-  if (sel) {
-    const int64_t r = static_cast<int64_t>(uniform_i32(d.prefix[j >> 6])) +
-                      __popcll(mj & ((uint64_t(1) << (j & 63)) - 1));
-    const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
-    const rsrc_t rM = make_rsrc(d.M + r * d.ld_state + e0, len * 4);
-    const rsrc_t rV = make_rsrc(d.V + r * d.ld_state + e0, len * 4);
-    const rsrc_t rW = make_rsrc(d.weight + j * d.ld_weight + e0, len * 2);
-    if (d.vec)
-      cm_adam_vec_any<kCmInplace, false>(d.cm_qpt, rG, rP, rM, rV, rW, rP, rM, rV, rW, c, ss);
-    else
-      cm_adam_elem<kCmInplace, false>(rG, rP, rM, rV, rW, rP, rM, rV, rW, c, len, ss);
-    cm_zero_rows(d, rOut, len);
-  } else if (d.vec) {
-    if (d.cm_qpt >= kCmQpt)
-      cm_interval_sum_vec<kCmQpt, false, true>(h, 0, q, j, e0, len, rG, rOut, scale, ss);
-    else
-      cm_interval_sum_vec<kCmQpt / 2, false, true>(h, 0, q, j, e0, len, rG, rOut, scale, ss);
-  } else {
-    cm_interval_sum_elem<false, true>(h, 0, q, j, e0, len, rG, rOut, scale, ss);
-  }
+  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    constexpr int P = decltype(path)::value;
+    const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
+    const rsrc_t rOut = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
+    if (sel) {
+      const int64_t r = static_cast<int64_t>(uniform_i32(d.prefix[j >> 6])) +
+                        __popcll(mj & ((uint64_t(1) << (j & 63)) - 1));
+      const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
+      const rsrc_t rM = make_rsrc(d.M + r * d.ld_state + e0, len * 4);
+      const rsrc_t rV = make_rsrc(d.V + r * d.ld_state + e0, len * 4);
+      const Row16 rW = row16(d.weight + j * d.ld_weight + e0, len);
+      cm_adam_piece<kCmInplace, false, false, P>(d.cm_qpt, rG, rP, rM, rV, rW, rP, rM, rV, rP, c,
+                                                 len, ss);
+      cm_zero_rows<P>(rOut, len);
+    } else {
+      cm_interval_sum_piece<false, true, P>(d.cm_qpt, h, 0, q, j, e0, len, rG, rOut, scale, ss);
+    }
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -796,100 +857,91 @@ __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
 // ---------------------------------------------------------------------------
 
 // The hand-over of rows [e0, e0 + len) of channel j, len <= QPT * 256 * 4
-// (QPT quads per lane on the vector path).
-template <bool STAGE, int QPT>
+// (QPT quads per lane on the vector paths).
+template <bool STAGE, int QPT, bool RAG>
 __device__ __forceinline__ void cm_unpack_rows(const DevMat& d, int64_t j, int64_t e0,
                                                int64_t len, float scale) {
   const int64_t w = j >> 6;
   const uint64_t mw = uniform_u64(d.mask[w]);
   const bool sel = (mw >> (j & 63)) & 1ull;
-  const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
-  const int tid = threadIdx.x;
-  if (sel) {
-    const float z[kQuad] = {0.f, 0.f, 0.f, 0.f};
-    if (d.vec) {
-#pragma unroll
-      for (int q = 0; q < QPT; ++q) f32x4_store<kAuxWO>(rD, quad_elem(q, tid) * 4, z);
-    } else {
-      for (int64_t e = tid; e < len; e += kThreads)
-        buf_put_f32<kAuxWO>(0.0f, rD, static_cast<uint32_t>(e) * 4, 0);
-    }
-    return;
-  }
   const int64_t u = j - (static_cast<int64_t>(uniform_i32(d.prefix[w])) +
                          __popcll(mw & ((uint64_t(1) << (j & 63)) - 1)));
-  const rsrc_t rA = make_rsrc(d.acc + u * d.ld_acc + e0, len * 4);
-  const rsrc_t rS = STAGE ? make_rsrc(d.acc1 + j * d.ld_acc1 + e0, len * 2) : rA;
-  if (d.vec) {
-    float a[QPT][kQuad];
-#pragma unroll
-    for (int q = 0; q < QPT; ++q) {
-      if constexpr (STAGE) widen4(buf_b64<kAuxRO>(rS, quad_elem(q, tid) * 2, 0), a[q]);
-      else f32x4_load<kAuxRO>(rA, quad_elem(q, tid) * 4, a[q]);
+  const int tid = threadIdx.x;
+  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    constexpr int P = decltype(path)::value;
+    const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
+    if (sel) {
+      cm_zero_rows<P>(rD, len);
+      return;
     }
+    const rsrc_t rA = make_rsrc(STAGE ? nullptr : d.acc + u * d.ld_acc + e0, STAGE ? 0 : len * 4);
+    const Row16 rS = STAGE ? row16(d.acc1 + j * d.ld_acc1 + e0, len) : Row16{rA, nullptr, 0u};
+    if constexpr (P != kPathElem) {
+      float a[QPT][kQuad];
 #pragma unroll
-    for (int q = 0; q < QPT; ++q) {
+      for (int q = 0; q < QPT; ++q) {
+        if constexpr (STAGE) widen4(ld4<P == kPathRag, kAuxRO>(rS, quad_elem(q, tid)), a[q]);
+        else f32x4_load<kAuxRO>(rA, quad_elem(q, tid) * 4, a[q]);
+      }
 #pragma unroll
-      for (int i = 0; i < kQuad; ++i) a[q][i] = a[q][i] * scale;
-      f32x4_store<kAuxWO>(rD, quad_elem(q, tid) * 4, a[q]);
+      for (int q = 0; q < QPT; ++q) {
+#pragma unroll
+        for (int i = 0; i < kQuad; ++i) a[q][i] = a[q][i] * scale;
+        f32x4_store<kAuxWO>(rD, quad_elem(q, tid) * 4, a[q]);
+      }
+    } else {
+      for (int64_t e = tid; e < len; e += kThreads) {
+        const uint32_t o = static_cast<uint32_t>(e) * 4;
+        const float a = STAGE ? widen_bf16(buf_u16<kAuxRO>(rS.r, static_cast<uint32_t>(e) * 2, 0))
+                              : buf_f32<kAuxRO>(rA, o, 0);
+        buf_put_f32<kAuxWO>(a * scale, rD, o, 0);
+      }
     }
-  } else {
-    for (int64_t e = tid; e < len; e += kThreads) {
-      const uint32_t o = static_cast<uint32_t>(e) * 4;
-      const float a = STAGE ? widen_bf16(buf_u16<kAuxRO>(rS, static_cast<uint32_t>(e) * 2, 0))
-                            : buf_f32<kAuxRO>(rA, o, 0);
-      buf_put_f32<kAuxWO>(a * scale, rD, o, 0);
-    }
-  }
+  });
 }
 
 // The same with deferred packing: rows [e0, e0 + len) of channel j of the
 // hand-over are scale times the interval's sum, its kept steps (the last
 // `kept` entries of h) and this plan's gradient, or +0.0 when selected.
-template <int QPT>
+template <int QPT, bool RAG>
 __device__ __forceinline__ void cm_handover_rows_deferred(const DevMat& d, int32_t q, int64_t j,
                                                           int64_t e0, int64_t len, float scale,
                                                           const HistTable& h, int32_t kept) {
   const uint64_t mw = uniform_u64(d.mask[j >> 6]);
-  const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
-  const int tid = threadIdx.x;
-  if ((mw >> (j & 63)) & 1ull) {
-    const float z[kQuad] = {0.f, 0.f, 0.f, 0.f};
-    if (d.vec) {
-#pragma unroll
-      for (int p = 0; p < QPT; ++p) f32x4_store<kAuxWO>(rD, quad_elem(p, tid) * 4, z);
-    } else {
-      for (int64_t e = tid; e < len; e += kThreads)
-        buf_put_f32<kAuxWO>(0.0f, rD, static_cast<uint32_t>(e) * 4, 0);
-    }
-    return;
-  }
-  const rsrc_t rG = make_rsrc(d.grad + j * d.ld_grad + e0, len * 2);
+  const bool sel = (mw >> (j & 63)) & 1ull;
   double ss = 0.0;  // (no statistics)
-  if (d.vec)
-    cm_interval_sum_vec<QPT, false, true>(h, h.n - kept, q, j, e0, len, rG, rD, scale, ss);
-  else
-    cm_interval_sum_elem<false, true>(h, h.n - kept, q, j, e0, len, rG, rD, scale, ss);
+  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    constexpr int P = decltype(path)::value;
+    const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
+    const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
+    if (sel)
+      cm_zero_rows<P>(rD, len);
+    else if constexpr (P == kPathElem)
+      cm_interval_sum_elem<false, true>(h, h.n - kept, q, j, e0, len, rG.r, rD, scale, ss);
+    else
+      cm_interval_sum_vec<QPT, false, true, P == kPathRag>(h, h.n - kept, q, j, e0, len, rG, rD,
+                                                           scale, ss);
+  });
 }
 
 // One unpack block's work: channel local / cm_unch, its chunk local %
 // cm_unch of kCmUnpackChunk rows.
-template <bool STAGE>
+template <bool STAGE, bool RAG>
 __device__ __forceinline__ void cm_unpack_unit(const DevMat& d, int64_t local, float scale) {
   const int64_t j = local / d.cm_unch;
   const int64_t e0 = (local % d.cm_unch) * kCmUnpackChunk;
   const int64_t len = min(static_cast<int64_t>(kCmUnpackChunk), d.n - e0);
-  cm_unpack_rows<STAGE, kCmUnpackQpt>(d, j, e0, len, scale);
+  cm_unpack_rows<STAGE, kCmUnpackQpt, RAG>(d, j, e0, len, scale);
 }
 
-template <bool BATCHED, bool STAGE>
+template <bool BATCHED, bool STAGE, bool RAG>
 __global__ __launch_bounds__(kThreads) void cm_unpack_kernel(const DevMat* __restrict__ mats,
                                                             const int64_t* __restrict__ off,
                                                             int32_t nmats, DevMat one,
                                                             float scale) {
   int64_t local;
   const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
-  cm_unpack_unit<STAGE>(d, local, scale);
+  cm_unpack_unit<STAGE, RAG>(d, local, scale);
 }
 
 // The hand-over of an interval that Zen-auto ended on the device: nothing
@@ -903,7 +955,7 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_kernel(const DevMat* __res
 // DEFP (deferred packing): the interval's sums are taken from the kept
 // gradients of its earlier steps (the last length - 1 entries of h) and this
 // plan's gradient, as the deferred update would have written them.
-template <bool DEFP>
+template <bool DEFP, bool RAG>
 __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* __restrict__ mats,
                                                                 const int64_t* __restrict__ off,
                                                                 int32_t nmats, int64_t units,
@@ -937,14 +989,14 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
     const bool pair = u + 1 < u1 && (local + 1) / d.cm_unch == j;
     const int64_t len = min(static_cast<int64_t>(pair ? 2 : 1) * kCmUnpackChunk, d.n - e0);
     if (pair) {
-      if constexpr (DEFP) cm_handover_rows_deferred<2 * kCmUnpackQpt>(d, lo, j, e0, len, scale, h, kept);
-      else if (from_stage) cm_unpack_rows<true, 2 * kCmUnpackQpt>(d, j, e0, len, scale);
-      else cm_unpack_rows<false, 2 * kCmUnpackQpt>(d, j, e0, len, scale);
+      if constexpr (DEFP) cm_handover_rows_deferred<2 * kCmUnpackQpt, RAG>(d, lo, j, e0, len, scale, h, kept);
+      else if (from_stage) cm_unpack_rows<true, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
+      else cm_unpack_rows<false, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       u += 2;
     } else {
-      if constexpr (DEFP) cm_handover_rows_deferred<kCmUnpackQpt>(d, lo, j, e0, len, scale, h, kept);
-      else if (from_stage) cm_unpack_rows<true, kCmUnpackQpt>(d, j, e0, len, scale);
-      else cm_unpack_rows<false, kCmUnpackQpt>(d, j, e0, len, scale);
+      if constexpr (DEFP) cm_handover_rows_deferred<kCmUnpackQpt, RAG>(d, lo, j, e0, len, scale, h, kept);
+      else if (from_stage) cm_unpack_rows<true, kCmUnpackQpt, RAG>(d, j, e0, len, scale);
+      else cm_unpack_rows<false, kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       u += 1;
     }
   }
@@ -952,15 +1004,23 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
 
 }  // namespace
 
-template <int OUT>
+template <int OUT, bool RAG>
 static void launch_cm_colnorm_t(const Table& t, const DevMat& one, dim3 grid, float scale,
                                 hipStream_t s) {
   if (t.mats != nullptr)
-    hipLaunchKernelGGL((cm_colnorm_kernel<true, OUT>), grid, dim3(kThreads), 0, s, t.mats, t.off,
-                       t.nmats, one, scale);
-  else
-    hipLaunchKernelGGL((cm_colnorm_kernel<false, OUT>), grid, dim3(kThreads), 0, s, t.mats,
+    hipLaunchKernelGGL((cm_colnorm_kernel<true, OUT, RAG>), grid, dim3(kThreads), 0, s, t.mats,
                        t.off, t.nmats, one, scale);
+  else
+    hipLaunchKernelGGL((cm_colnorm_kernel<false, OUT, RAG>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, one, scale);
+}
+
+template <bool RAG>
+static void launch_cm_colnorm_out(const Table& t, const DevMat& one, dim3 grid, int32_t out,
+                                  float scale, hipStream_t s) {
+  if (out == 1) launch_cm_colnorm_t<1, RAG>(t, one, grid, scale, s);
+  else if (out == 2) launch_cm_colnorm_t<2, RAG>(t, one, grid, scale, s);
+  else launch_cm_colnorm_t<0, RAG>(t, one, grid, scale, s);
 }
 
 hipError_t launch_cm_colnorm(const Table& t, const DevMat& one, int64_t blocks, hipStream_t s,
@@ -968,9 +1028,8 @@ hipError_t launch_cm_colnorm(const Table& t, const DevMat& one, int64_t blocks, 
   (void)hipGetLastError();
   if (blocks > 0) {
     const dim3 grid(static_cast<uint32_t>(blocks));
-    if (out == 1) launch_cm_colnorm_t<1>(t, one, grid, scale, s);
-    else if (out == 2) launch_cm_colnorm_t<2>(t, one, grid, scale, s);
-    else launch_cm_colnorm_t<0>(t, one, grid, scale, s);
+    if (t.ragged) launch_cm_colnorm_out<true>(t, one, grid, out, scale, s);
+    else launch_cm_colnorm_out<false>(t, one, grid, out, scale, s);
   }
   return hipGetLastError();
 }
@@ -982,20 +1041,35 @@ hipError_t launch_cm_colnorm(const Table& t, const DevMat& one, int64_t blocks, 
 #endif
 constexpr unsigned kCmUpdateLds = ZF_CM_UPDATE_LDS;
 
+template <bool ADAM, bool PACK, bool STATS, bool HAND, bool PEND, bool SELG, int PH, bool RAG>
+static void launch_cm_update_r(const Table& t, const DevMat& one, dim3 grid, const AdamK& c,
+                               int32_t mode, int32_t first, double* zs, float scale,
+                               hipStream_t s, const Pending& pd, const ZenState* zst) {
+  if (t.mats != nullptr)
+    hipLaunchKernelGGL((cm_update_kernel<true, ADAM, PACK, STATS, HAND, PEND, SELG, PH, false, RAG>),
+                       grid, dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode,
+                       first, zs, scale, pd, zst, HistTable{});
+  else
+    hipLaunchKernelGGL(
+        (cm_update_kernel<false, ADAM, PACK, STATS, HAND, PEND, SELG, PH, false, RAG>), grid,
+        dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode, first, zs, scale,
+        pd, zst, HistTable{});
+}
+
+// The interval's phase is a compile-time constant in the aligned launches of
+// the fixed schedule; the ragged kernels, larger already, take it at run time.
 template <bool ADAM, bool PACK, bool STATS, bool HAND, bool PEND = false, bool SELG = false,
           int PH = 0>
 static void launch_cm_update_t(const Table& t, const DevMat& one, dim3 grid, const AdamK& c,
                                int32_t mode, int32_t first, double* zs, float scale,
                                hipStream_t s, const Pending& pd = Pending{},
                                const ZenState* zst = nullptr) {
-  if (t.mats != nullptr)
-    hipLaunchKernelGGL((cm_update_kernel<true, ADAM, PACK, STATS, HAND, PEND, SELG, PH>), grid,
-                       dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode,
-                       first, zs, scale, pd, zst, HistTable{});
+  if (t.ragged)
+    launch_cm_update_r<ADAM, PACK, STATS, HAND, PEND, SELG, 0, true>(t, one, grid, c, mode, first,
+                                                                     zs, scale, s, pd, zst);
   else
-    hipLaunchKernelGGL((cm_update_kernel<false, ADAM, PACK, STATS, HAND, PEND, SELG, PH>), grid,
-                       dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode,
-                       first, zs, scale, pd, zst, HistTable{});
+    launch_cm_update_r<ADAM, PACK, STATS, HAND, PEND, SELG, PH, false>(t, one, grid, c, mode,
+                                                                       first, zs, scale, s, pd, zst);
 }
 
 // The fused update (HAND: with the hand-over) with its interval phase as a
@@ -1067,14 +1141,14 @@ hipError_t launch_cm_update(const Table& t, const DevMat& one, int64_t blocks, c
   return hipGetLastError();
 }
 
-template <bool STAGE>
+template <bool STAGE, bool RAG>
 static void launch_cm_unpack_t(const Table& t, const DevMat& one, dim3 grid, float scale,
                                hipStream_t s) {
   if (t.mats != nullptr)
-    hipLaunchKernelGGL((cm_unpack_kernel<true, STAGE>), grid, dim3(kThreads), 0, s, t.mats, t.off,
-                       t.nmats, one, scale);
+    hipLaunchKernelGGL((cm_unpack_kernel<true, STAGE, RAG>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, one, scale);
   else
-    hipLaunchKernelGGL((cm_unpack_kernel<false, STAGE>), grid, dim3(kThreads), 0, s, t.mats,
+    hipLaunchKernelGGL((cm_unpack_kernel<false, STAGE, RAG>), grid, dim3(kThreads), 0, s, t.mats,
                        t.off, t.nmats, one, scale);
 }
 
@@ -1084,9 +1158,29 @@ hipError_t launch_cm_handover_deferred(const Table& t, const DevMat& one, int64_
   (void)hipGetLastError();
   (void)one;
   if (blocks <= 0 || t.mats == nullptr) return hipSuccess;
-  hipLaunchKernelGGL(cm_handover_deferred_kernel, dim3(static_cast<uint32_t>(blocks)),
-                     dim3(kThreads), 0, s, t.mats, t.off, t.nmats, c, scale, h);
+  const dim3 grid(static_cast<uint32_t>(blocks));
+  if (t.ragged)
+    hipLaunchKernelGGL(cm_handover_deferred_kernel<true>, grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, c, scale, h);
+  else
+    hipLaunchKernelGGL(cm_handover_deferred_kernel<false>, grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, c, scale, h);
   return hipGetLastError();
+}
+
+template <bool RAG>
+static void launch_cm_zen_deferred_t(const Table& t, const DevMat& one, dim3 grid, const AdamK& c,
+                                     int32_t mode, double* zs, bool handover, const HistTable& h,
+                                     const ZenState* zst, hipStream_t s) {
+  if (handover)
+    hipLaunchKernelGGL((cm_update_kernel<true, true, true, true, true, false, false, 0, true, RAG>),
+                       grid, dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c,
+                       mode, 1, zs, 1.0f, Pending{}, zst, h);
+  else
+    hipLaunchKernelGGL(
+        (cm_update_kernel<true, true, true, true, false, false, false, 0, true, RAG>), grid,
+        dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode, 1, zs, 1.0f,
+        Pending{}, zst, h);
 }
 
 hipError_t launch_cm_update_zen_deferred(const Table& t, const DevMat& one, int64_t blocks,
@@ -1097,14 +1191,10 @@ hipError_t launch_cm_update_zen_deferred(const Table& t, const DevMat& one, int6
   if (blocks <= 0 || t.mats == nullptr) return hipSuccess;
   if (zs == nullptr || zst == nullptr) return hipErrorInvalidValue;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  if (handover)
-    hipLaunchKernelGGL((cm_update_kernel<true, true, true, true, true, false, false, 0, true>),
-                       grid, dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c,
-                       mode, 1, zs, 1.0f, Pending{}, zst, h);
+  if (t.ragged)
+    launch_cm_zen_deferred_t<true>(t, one, grid, c, mode, zs, handover, h, zst, s);
   else
-    hipLaunchKernelGGL((cm_update_kernel<true, true, true, true, false, false, false, 0, true>),
-                       grid, dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c,
-                       mode, 1, zs, 1.0f, Pending{}, zst, h);
+    launch_cm_zen_deferred_t<false>(t, one, grid, c, mode, zs, handover, h, zst, s);
   return hipGetLastError();
 }
 
@@ -1116,8 +1206,12 @@ hipError_t launch_cm_unpack_zen(const Table& t, const DevMat& one, int64_t units
   (void)one;
   if (units <= 0 || t.mats == nullptr) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(units < kCmUnpackZenGrid ? units : kCmUnpackZenGrid));
-  hipLaunchKernelGGL(cm_unpack_zen_kernel<false>, grid, dim3(kThreads), 0, s, t.mats, t.off,
-                     t.nmats, units, zst, stage ? 1 : 0, HistTable{});
+  if (t.ragged)
+    hipLaunchKernelGGL((cm_unpack_zen_kernel<false, true>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, units, zst, stage ? 1 : 0, HistTable{});
+  else
+    hipLaunchKernelGGL((cm_unpack_zen_kernel<false, false>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, units, zst, stage ? 1 : 0, HistTable{});
   return hipGetLastError();
 }
 
@@ -1126,8 +1220,12 @@ hipError_t launch_cm_unpack_zen_deferred(const Table& t, int64_t units, const Hi
   (void)hipGetLastError();
   if (units <= 0 || t.mats == nullptr) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(units < kCmUnpackZenGrid ? units : kCmUnpackZenGrid));
-  hipLaunchKernelGGL(cm_unpack_zen_kernel<true>, grid, dim3(kThreads), 0, s, t.mats, t.off,
-                     t.nmats, units, zst, 0, h);
+  if (t.ragged)
+    hipLaunchKernelGGL((cm_unpack_zen_kernel<true, true>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, units, zst, 0, h);
+  else
+    hipLaunchKernelGGL((cm_unpack_zen_kernel<true, false>), grid, dim3(kThreads), 0, s, t.mats,
+                       t.off, t.nmats, units, zst, 0, h);
   return hipGetLastError();
 }
 
@@ -1136,8 +1234,10 @@ hipError_t launch_cm_unpack(const Table& t, const DevMat& one, int64_t blocks, f
   (void)hipGetLastError();
   if (blocks > 0) {
     const dim3 grid(static_cast<uint32_t>(blocks));
-    if (from_stage) launch_cm_unpack_t<true>(t, one, grid, scale, s);
-    else launch_cm_unpack_t<false>(t, one, grid, scale, s);
+    if (from_stage && t.ragged) launch_cm_unpack_t<true, true>(t, one, grid, scale, s);
+    else if (from_stage) launch_cm_unpack_t<true, false>(t, one, grid, scale, s);
+    else if (t.ragged) launch_cm_unpack_t<false, true>(t, one, grid, scale, s);
+    else launch_cm_unpack_t<false, false>(t, one, grid, scale, s);
   }
   return hipGetLastError();
 }

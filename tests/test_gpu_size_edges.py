@@ -122,29 +122,80 @@ def test_row_major_zen_against_channel_major(n, m):
                 assert rel_close(b, a, 2.0 ** -22)[0], (form, n, m, t)
 
 
-# Row-major plain steps on gradient rows of an odd number of elements: the
-# 16-byte kernel (all phases, with and without the bf16 stage, the deferred
-# hand-over) against the oracle, bit for bit, through the runner.
+# The runner on rows of any alignment, bit for bit against the oracle.
+# Row-major: gradient rows of an odd number of elements through the 16-byte
+# kernel (all phases, with and without the bf16 stage, the deferred hand-over).
+# Channel-major: channels of n % 8 != 0 through the ragged kernels, n at the
+# edges of a quad, a lane's quads and a chunk, next to an aligned matrix.
+def _odd_runner(layout, shapes, how):
+    cm = layout == zf.CHANNEL_MAJOR
+    R, S, T = 8, 4, 9
+    hp = zf.AdamHparams(lr=1e-3, weight_decay=0.01)
+
+    def dev(b):
+        return bf16_dev(np.ascontiguousarray(b.T) if cm else b)
+
+    def host(t):
+        x = bits_np(t) if t.dtype == torch.bfloat16 else f32_np(t)
+        return np.ascontiguousarray(x.T) if cm else x
+
+    bits = [[gbits(n, m, 100 * n + m + t) for n, m in shapes] for t in range(4)]
+    w = [O.bf16_round((0.02 * np.random.default_rng(n).standard_normal((n, m))).astype(np.float32))
+         for n, m in shapes]
+    wd = [dev(x) for x in w]
+    r = zf.SelectiveUpdateRunner(shapes, 0.1, hp, R, S, [[dev(b) for b in s] for s in bits], wd,
+                                 layout=layout, first_step_stage=how == "stage",
+                                 deferred_pack=how == "deferred",
+                                 fuse_handover=how != "separate")
+    orc = [O.MatrixOracle(O.widen(x), x, 0.1, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay,
+                          R, S) for x in w]
+    for t in range(1, T + 1):
+        kind = r.step()
+        torch.cuda.synchronize()
+        for q, o in enumerate(orc):
+            want = o.step(bits[(t - 1) % 4][q])
+            assert np.array_equal(host(wd[q]), o.W), (t, q)
+            for got, exp in zip(r.state[q], (o.P, o.M, o.V)):
+                assert same_bits(host(got), exp), (t, q)
+            if kind.interval_end:
+                assert same_bits(host(r.unpacked[q]), want["unpacked"]), (t, q)
+
+
 @pytest.mark.parametrize("shape", [(33, 1003), (130, 965), (7, 9), (64, 2049)])
 @pytest.mark.parametrize("how", ["stage", "plain", "deferred"])
 def test_row_major_odd_rows_runner(shape, how):
-    n, m = shape
-    rng = np.random.default_rng(n + m)
-    R, S = 8, 4
-    bits = [gbits(n, m, 100 * n + m + t) for t in range(4)]
-    w = O.bf16_round((0.02 * rng.standard_normal((n, m))).astype(np.float32))
-    hp = zf.AdamHparams(lr=1e-3, weight_decay=0.01)
-    wd = bf16_dev(w)
-    r = zf.SelectiveUpdateRunner([shape], 0.1, hp, R, S, [[bf16_dev(b)] for b in bits], [wd],
-                                 first_step_stage=how == "stage", deferred_pack=how == "deferred")
-    orc = O.MatrixOracle(O.widen(w), w, 0.1, hp.lr, hp.beta1, hp.beta2, hp.eps, hp.weight_decay,
-                         R, S)
-    for t in range(1, 9):
-        kind = r.step()
-        want = orc.step(bits[(t - 1) % 4])
-        torch.cuda.synchronize()
-        assert np.array_equal(bits_np(wd), orc.W), t
-        for got, exp in zip(r.state[0], (orc.P, orc.M, orc.V)):
-            assert same_bits(f32_np(got), exp), t
-        if kind.interval_end:
-            assert same_bits(f32_np(r.unpacked[0]), want["unpacked"]), t
+    _odd_runner(zf.ROW_MAJOR, [shape], how)
+
+
+@pytest.mark.parametrize("n", [1, 3, 5, 255, 1027, 2047, 2049, 4099])
+@pytest.mark.parametrize("how", ["stage", "plain", "separate", "deferred"])
+def test_channel_major_odd_channels_runner(n, how):
+    _odd_runner(zf.CHANNEL_MAJOR, [(n, 21), (64, 10)], how)
+
+
+# Channel-major scores of channels of any length: whole groups of eight, the
+# rows after them, and both stores a refresh may ride on the pass.
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 511, 513, 2048, 2055, 4099])
+def test_channel_major_odd_scores(n):
+    m, dev = 13, torch.device("cuda")
+    g = gbits(n, m, n)
+    want = (O.widen(g).astype(np.float64) ** 2).sum(0)
+    for offset in (0, 1, 3):
+        G = bf16_dev(np.ascontiguousarray(g.T), offset=offset)
+        norms = torch.zeros(m, device=dev)
+        out = torch.full((m, n), float("nan"), device=dev)
+        stage = torch.zeros(m, n, dtype=torch.bfloat16, device=dev)
+        w, acc = torch.zeros_like(stage), torch.zeros(m - 1, n, device=dev)
+        st = [torch.zeros(1, n, device=dev) for _ in range(3)]
+        plan = zf.Plan([zf.MatrixBuffers(
+            grad=G, k=1, sel=zf.Selection(m, 1), weight=w, master=st[0], exp_avg=st[1],
+            exp_avg_sq=st[2], acc=acc, norms=norms, unpacked=out, acc_first=stage,
+            layout=zf.CHANNEL_MAJOR)])
+        for call in (plan.colnorm, plan.colnorm_stage, lambda: plan.colnorm_handover(0.5)):
+            norms.zero_()
+            call()
+            torch.cuda.synchronize()
+            assert rel_close(f32_np(norms), want, 2.0 ** -23)[0], (n, offset)
+        assert np.array_equal(bits_np(stage), g.T), (n, offset)
+        assert same_bits(f32_np(out), O.widen(g).T * np.float32(0.5)), (n, offset)
+        plan.close()
