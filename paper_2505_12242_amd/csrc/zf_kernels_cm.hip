@@ -542,7 +542,11 @@ __device__ __forceinline__ void cm_interval_sum_vec(const HistTable& h, int32_t 
                                                     const Row16& rG, rsrc_t rOut, float scale,
                                                     double& ss) {
   const int tid = threadIdx.x;
-  constexpr int kBatch = 4;  // steps whose rows are loaded before they are added
+  // steps whose rows are loaded before they are added: 8 against 4, hand-over
+  // of a Llama-2-70B layer (8 steps) 3221 -> 3169 us, of a 7B layer (4 steps, the
+  // loop then runs once) 422 -> 410; 2 measured as 4.  With the statistics 4: a
+  // Zen-auto period of a 7B layer 1261 us against 1283 with 8.
+  constexpr int kBatch = STATS ? 4 : 8;
   float a[QPT][kQuad];
   const int32_t steps = h.n - s_first + 1;  // the kept steps, then this one
   for (int32_t s0 = 0; s0 < steps; s0 += kBatch) {
