@@ -576,6 +576,16 @@ zf_status run_update(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
   finish_geometry(d, 256, pick_update_rows({{n, m}}));
   set_rv(d, pick_rv_rows({{n, m}}), true);
   if (layout == zf::kRowMajor && !rm_strides_ok(d)) return ZF_EINVAL;
+  const int64_t sel_blocks = k * static_cast<int64_t>(d.cm_snch);
+  if (layout == zf::kChannelMajor && adam && !pack && d.st_P == nullptr &&
+      sel_blocks <= ((int64_t(1) << 32) - 1) / zf::kThreads) {
+    // Adam alone: a grid of the selected channels, as a plan's (within one
+    // launch's work-items); the full grid's other blocks only read the mask.
+    // 10% of 11008 x 4096 24.2 against 30.0 us, of 28672 x 8192 119 against 139.
+    const hipError_t e = zf::launch_cm_adam_selected_grid(single_table(d), d, sel_blocks, c, mode,
+                                                          as_stream(stream));
+    return e == hipSuccess ? ZF_OK : hip_fail(e);
+  }
   const bool rv = use_rv(d, mode, adam, pack, d.vec != 0, n * m);
   const int64_t blocks = rv ? rv_grid(d) : update_grid(d);
   if (blocks == 0) return ZF_OK;
