@@ -69,11 +69,8 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 //   hand-over, deferred  7B layer (52 K blocks) 423 / 430 / 441, 3 layers and
 //                        embeddings (220 K) 2210 / 2190 / 2196, 12 (690 K) 6915 /
 //                        6757 / 6778, 20 (1.1 M) 11170 / 10930 / 10900
-//   row-major update     a 7B layer's pass (30 K blocks) 2224 / - / 2328, a small
-//                        layer's 147 / - / 159; in place, 2 / 4 / 8 / 16 layers (60 /
-//                        120 / 120 / 240 K), runs of 64 against one range, each layer:
-//                        617 / 640 / 637 / 594 and 612 / 575 / 549 / 546 (second
-//                        step 564 / 607 / 626 / 583 and 544 / 521 / 500 / 504)
+//   row-major update     7B layer (15 K larger blocks) 696 / 700 / 727, the 7B
+//                        set's deferred hand-over (490 K) - / 23300 / 22400
 //   Adam, selected grid  13B layer (79 K) 457 / 451 / 469, 70B (84 K) 450 / 436 /
 //                        440, 12 7B layers (265 K) 1405 / 1383 / 1381, 20 (430 K)
 //                        2273 / 2240 / 2222
@@ -90,7 +87,7 @@ __device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B) {
   if constexpr (ZF_XCD_REMAP == 0) return b;
   uint32_t lg;  // log2 RUN, or 0: one range per XCD
   if constexpr (ORDER == kOrderScores) lg = B <= (1u << 17) ? 6 : 0;
-  else if constexpr (ORDER == kOrderRowMajor) lg = B <= (1u << 16) ? 6 : 0;
+  else if constexpr (ORDER == kOrderRowMajor) lg = B <= (1u << 17) ? 6 : 0;
   else if constexpr (ORDER == kOrderSelected) lg = B <= (1u << 18) ? 8 : 0;
   else lg = B <= (1u << 17) ? 6 : B <= (1u << 20) ? 8 : 0;
   const uint32_t full = lg != 0 ? B >> (lg + 3) << (lg + 3) : 0;
