@@ -541,7 +541,8 @@ zf_status zf_plan_update_handover(zf_plan* plan, const zf_adam_hparams* hp, int6
  * earlier: HOST array of n_earlier (1..15) plans over the same matrices in
  * the same order (same n, m, k; channel-major: the same access path), in
  * step order, whose descriptors' grad is the gradient of that step; only
- * those gradients are read.  They must not overlap what this step writes.
+ * those gradients are read (row-major whole, so that every one must be
+ * given, also where k = m).  They must not overlap what this step writes.
  * Both layouts, plans without a full-state store; `unpacked` required;
  * scale finite.  Row-major: two launches, the Adam-only pass and a
  * hand-over pass (the 16-byte kernels unless a row stride is too long for

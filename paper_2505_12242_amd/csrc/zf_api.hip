@@ -1377,7 +1377,9 @@ zf_status gather_earlier(const zf_plan* p, const zf_plan* const* earlier, int32_
       if (cm && (a.vec != b.vec || a.cm_qpt != b.cm_qpt || a.cm_nch != b.cm_nch ||
                  a.cm_snch != b.cm_snch || a.cm_unch != b.cm_unch))
         return ZF_EINVAL;
-      if (b.n * (b.m - b.k) > 0 && a.grad == nullptr) return ZF_EINVAL;
+      // channel-major the unselected channels of an earlier gradient are read,
+      // row-major every column (the selected ones share their cache lines)
+      if (b.n * (cm ? b.m - b.k : b.m) > 0 && a.grad == nullptr) return ZF_EINVAL;
       if (!cm) {
         // the row blocks of this plan's kernels address the earlier rows
         // through the same 32-bit offsets

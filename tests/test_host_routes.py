@@ -1,0 +1,175 @@
+"""Which kernels a call launches, and what it refuses, without a GPU.
+
+The library's host side is run in a process of its own in which the HIP
+runtime's launches and copies are replaced by ones that only take notes
+(tests/native/hip_record.cpp).  Fake device addresses are never read."""
+import ctypes
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from tests.conftest import ROOT
+
+RM, CM = 0, 1
+INPLACE, REMAP, INIT = 0, 1, 2
+EINVAL = 1
+
+
+# ---------------------------------------------------------------------------
+# the recording process
+# ---------------------------------------------------------------------------
+
+class Recorder:
+    def __init__(self):
+        from paper_2505_12242_amd import _lib
+        self.L = _lib
+        self.rec = ctypes.CDLL(os.environ["ZF_RECORDER"])
+        self.buf = ctypes.create_string_buffer(1 << 16)
+        self.hp = _lib.ZfAdamHparams(1e-5, 0.9, 0.999, 1e-8, 0.0)
+        self.top = 0x7F0000000000
+        self.state = self.addr(64, 0)
+        self.names = {}
+
+    def addr(self, nbytes, off):
+        """A fresh fake address, `off` bytes past a 4 KiB boundary."""
+        p = self.top + off
+        self.top += (nbytes + off + 8192) & ~4095
+        return p
+
+    def matrix(self, n, m, layout, off16=0, off32=0, zen=False, grad=True, ld=None, acc=True,
+               stage=False, ratio=0.1):
+        """off16 / off32: bytes the bf16 gradient / the fp32 buffers start past
+        a 16-byte boundary; ld: the weight's row stride in elements."""
+        k = self.L.LIB.zf_k_from_ratio(ratio, m)
+        x = self.L.ZfMatrix()
+        x.n, x.m, x.k, x.layout = n, m, k, layout
+        rows, cols = (n, m) if layout == RM else (m, n)
+
+        def store(r, c, size, off=0, stride=None):
+            """(address, stride): rows padded to 16 bytes unless off is given."""
+            per = 16 // size
+            s = stride or (c if off or layout == CM else max(per, -(-c // per) * per))
+            return self.addr(max(r, 1) * s * size, off), s
+
+        def part(count):  # n x count in the layout
+            return (n, count) if layout == RM else (count, n)
+
+        if grad:
+            x.grad, x.ld_grad = store(rows, cols, 2, off16)
+        else:
+            x.grad, x.ld_grad = None, cols
+        x.weight, x.ld_weight = store(rows, cols, 2, stride=ld)
+        for name in ("master", "exp_avg", "exp_avg_sq"):
+            p, x.ld_state = store(*part(k), 4, off32)
+            setattr(x, name, p)
+        if acc:
+            x.acc, x.ld_acc = store(*part(m - k), 4, off32)
+        x.unpacked, x.ld_unpacked = store(rows, cols, 4, off32)
+        x.norms_sq = self.addr(4 * m, 0)
+        x.sel = self.L.ZfSelection(self.addr(4 * m, 0), self.addr(4 * m, 0), self.addr(m, 0),
+                                   self.addr(m, 0))
+        if zen:
+            x.sel_sq, x.acc_sq = self.addr(4 * m, 0), self.addr(4 * m, 0)
+        if stage:
+            x.acc_first, x.ld_acc_first = store(rows, cols, 2)
+        return x
+
+    def plan(self, mats):
+        arr = (self.L.ZfMatrix * len(mats))(*mats)
+        nbytes, h = ctypes.c_size_t(), ctypes.c_void_p()
+        st = self.L.LIB.zf_plan_query(arr, len(mats), ctypes.byref(nbytes))
+        assert st == 0, st
+        st = self.L.LIB.zf_plan_create(arr, len(mats), self.addr(nbytes.value, 0), nbytes.value,
+                                       None, ctypes.byref(h))
+        assert st == 0, st
+        return h
+
+    def call(self, fn, *args):
+        """[status, [[kernel, grid, block], ...]]"""
+        self.rec.rec_take(self.buf, len(self.buf))
+        st = getattr(self.L.LIB, fn)(*args)
+        self.rec.rec_take(self.buf, len(self.buf))
+        out = []
+        for ln in self.buf.value.decode().splitlines():
+            name, grid, block = ln.rsplit(" ", 2)
+            out.append([self.demangle(name), int(grid), int(block)])
+        return [st, out]
+
+    def demangle(self, name):
+        if name not in self.names:
+            s = subprocess.run(["c++filt", name], capture_output=True, text=True).stdout.strip()
+            s = s.replace("(anonymous namespace)::", "").replace("void ", "").replace("zf::", "")
+            self.names[name] = s.split("(")[0]
+        return self.names[name]
+
+    # the calls -------------------------------------------------------------
+    def update(self, p, mode=INPLACE, sii=3, adam=1, pack=1):
+        return self.call("zf_plan_update", p, ctypes.byref(self.hp), 5, mode, sii, 8, adam, pack,
+                         None)
+
+    def deferred(self, p, earlier):
+        hs = (ctypes.c_void_p * len(earlier))(*[e.value for e in earlier])
+        return self.call("zf_plan_update_handover_deferred", p, ctypes.byref(self.hp), 5, hs,
+                         len(earlier), 0.25, None)
+
+
+def scenarios(r):
+    out = {}
+    # deferred hand-over, an earlier step without a gradient
+    for layout in (RM, CM):
+        for off in (0, 2):
+            for ratio in (0.1, 1.0):
+                a = [r.matrix(64, 72, layout, off16=off, ratio=ratio)]
+                e = [r.matrix(64, 72, layout, off16=off, ratio=ratio)]
+                none = [r.matrix(64, 72, layout, off16=off, ratio=ratio, grad=False)]
+                if layout == CM and off:  # the same access path as the plan's
+                    none[0].weight += 2
+                p = r.plan(a)
+                out[f"no-grad {layout} {off} {ratio}"] = [r.deferred(p, [r.plan(e)]),
+                                                          r.deferred(p, [r.plan(none)])]
+    return out
+
+
+if __name__ == "__main__":
+    print("RESULT " + json.dumps(scenarios(Recorder())))
+    sys.exit(0)
+
+
+# ---------------------------------------------------------------------------
+# the tests
+# ---------------------------------------------------------------------------
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None or shutil.which("c++filt") is None:
+        pytest.skip("g++ and c++filt needed")
+    so = str(tmp_path_factory.mktemp("rec") / "librec.so")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so,
+                    os.path.join(ROOT, "tests", "native", "hip_record.cpp"), "-ldl"], check=True)
+    pre = os.environ.get("LD_PRELOAD", "")
+    env = dict(os.environ, LD_PRELOAD=so + (":" + pre if pre else ""), ZF_RECORDER=so)
+    run = subprocess.run([sys.executable, "-m", "tests.test_host_routes"], cwd=ROOT, env=env,
+                         capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, run.stdout + run.stderr
+    line = [x for x in run.stdout.splitlines() if x.startswith("RESULT ")][-1]
+    return json.loads(line[len("RESULT "):])
+
+
+@pytest.mark.parametrize("off", [0, 2])
+@pytest.mark.parametrize("ratio", [0.1, 1.0])
+def test_deferred_handover_needs_the_earlier_gradients(routes, off, ratio):
+    """Row-major, the hand-over reads whole rows of every earlier gradient,
+    the selected columns too: a plan without one is refused whatever k.
+    Channel-major reads the unselected channels only: with k = m there are
+    none."""
+    with_grad, without = routes[f"no-grad {RM} {off} {ratio}"]
+    assert with_grad[0] == 0 and len(with_grad[1]) == 2
+    assert without == [EINVAL, []]
+    with_grad, without = routes[f"no-grad {CM} {off} {ratio}"]
+    assert with_grad[0] == 0 and len(with_grad[1]) == 1
+    assert without[0] == (0 if ratio == 1.0 else EINVAL)
