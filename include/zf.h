@@ -58,9 +58,12 @@
  *           (row r = column sel_idx[r]), A is [m-k][ld_acc >= n] (row u =
  *           column unsel_idx[u]).  Results are identical in both layouts.
  *           Row-major update steps with the states in place (and pack-only
- *           calls) run a kernel with 16-byte accesses, refresh steps (and
- *           Adam-only steps of small matrices whose gradient rows are not
- *           16-byte aligned) a per-column kernel.  The results are identical.
+ *           calls) run a kernel with 16-byte accesses when G is 16-byte
+ *           aligned with ld % 8 == 0 and A, P/M/V and the hand-over output
+ *           (those the call uses) are 16-byte aligned with ld % 4 == 0, or
+ *           when the matrices are wide and large enough that it is the faster
+ *           all the same; otherwise, and on refresh steps, a per-column
+ *           kernel.  The results are identical.
  * Selection.  sel_idx[k] and unsel_idx[m-k] are ascending column indices;
  *           sel_mask[ceil(m/64)] has bit b of word w set iff column 64w+b is
  *           selected (bits at columns >= m are 0); sel_prefix[ceil(m/64)]
@@ -545,9 +548,7 @@ zf_status zf_plan_update_handover(zf_plan* plan, const zf_adam_hparams* hp, int6
  * given, also where k = m).  They must not overlap what this step writes.
  * Both layouts, plans without a full-state store; `unpacked` required;
  * scale finite.  Row-major: two launches, the Adam-only pass and a
- * hand-over pass (the 16-byte kernels unless a row stride is too long for
- * them);
- * the hand-over pass reads every element of each step's gradient, since
+ * hand-over pass, which reads every element of each step's gradient, since
  * the selected columns share their cache lines.  ZF_EINVAL (nothing
  * enqueued) on a mismatch or when an earlier gradient's row stride does
  * not fit the plan's row blocks.  The kernels read the earlier plans'
@@ -626,11 +627,10 @@ typedef struct zf_zen_totals {
  * 1/step_in_interval) when trigger is set; the next step then starts a new
  * interval (step_in_interval = 1).
  * Channel-major plans sum the squares inside the update pass.  Row-major
- * plans do too (on refresh steps the packing pass sums them, after the Adam
- * pass), but for row strides too long for the 16-byte update, and with the
- * owed deferred update, where they run the update and then a separate
- * statistics pass that reads the selected gradient columns and the packed
- * buffer again.  Both row-major forms write the same fp64
+ * plans that take the 16-byte update (see Layouts) do too (on refresh steps
+ * the packing pass sums them, after the Adam pass); the others, and a refresh
+ * with the owed deferred update, run the update and then a separate statistics
+ * pass that reads the selected gradient columns and the packed buffer again.  Both row-major forms write the same fp64
  * partials (per column and row block, in row order) to the plan's
  * column-score workspace, so they give identical statistics; the two layouts
  * agree up to the order of the fp64 sums.

@@ -400,10 +400,10 @@ bool cm_vec_ok(const DevMat& d) {
          ok(d.acc1, d.ld_acc1, 8);
 }
 
-// Row-major 16-byte update: any gradient rows (16-byte loads of any alignment);
-// the fp32 buffers moved in slot quads or column quads (A, P/M/V, the hand-over
-// output) in 16-byte accesses at 4-byte alignment.  Other buffers are accessed
-// by element.
+// The row-major 16-byte update can run on any rows: gradient rows in 16-byte
+// loads of any alignment, the fp32 buffers moved in slot quads or column quads
+// (A, P/M/V, the hand-over output) in 16-byte accesses at 4-byte alignment,
+// the others by element.  Where it does: rv_pays.
 bool rv_ok(const DevMat& d) {
   return ZF_RV_ENABLE && d.layout == zf::kRowMajor && d.grad != nullptr;
 }
@@ -481,16 +481,52 @@ int64_t unpack_grid(const DevMat& d) {
 // runs the per-column kernel, which measured faster there.  Both give the same
 // bits.
 //
-// An Adam-only step whose gradient rows are not 16-byte aligned (g16 false)
-// runs the per-column kernel below kSmallAdam elements, which reads only the
-// selected columns' pieces of G: 4096 x 4095 24.2 against 33.1 us, 11008 x 4095
-// 77 against 70.
-constexpr int64_t kSmallAdam = int64_t(1) << 25;
+// With every buffer of the update in 16-byte rows it always does.  Off that
+// alignment its 16-byte accesses straddle lines and the two kernels are close,
+// so the line lies where it stops losing.  Over all matrices of a call: RmSet.
+//   - A tile of a narrow matrix leaves most of the block's lanes without a
+//     group of columns.  16-byte / per-column, in us, fused step in place:
+//     4 M elements of 33 columns 126 / 36, of 129 42 / 21, of 301 28 / 18; 134 M
+//     of 1023 (tiles of 512) 590 / 364, of 2001 (tiles of 704) 348 / 366.
+//     Hence tiles of 640 columns on average.
+//   - The latency of its two barriers shows on small sets.  Wide ones, cold
+//     caches: 16 M elements 0.94 - 1.15 of the per-column time (in the caches
+//     1.2 - 1.6), 33 M 0.91 - 1.05 at 10% selected (1.0 - 1.14 at 25%), 134 M
+//     0.92 - 1.02 (0.96 - 1.10).  Adam alone or packing alone leave it less to
+//     share a row with: 33 M in the caches 1.1 - 1.4, 67 M 0.89 - 1.0.
+//   - With the Zen-auto statistics it saves the pass that reads the packed
+//     buffer back: 16 M 0.75 - 0.99, 134 M 0.70 - 0.85 (tiles of 512: 1.1 - 1.2).
+//   - The deferred hand-over adds whole rows where the per-column pass gathers
+//     2-byte elements: 4 M 0.6 - 0.9, 134 M 0.3 - 0.4; 33 columns 1.2 (1 M: 1.9).
+struct RmSet {
+  bool al16 = true;    // every buffer of the update in 16-byte rows
+  int64_t elems = 0;   // rows x columns
+  int64_t rows = 0;    // rows of tiles: rows x column tiles
+  void add(const DevMat& d) {
+    // (a single row never uses its stride)
+    const auto ok = [&d](const void* p, int64_t ld, int64_t per16) {
+      return p == nullptr || (aligned(p, 16) && (d.n <= 1 || ld % per16 == 0));
+    };
+    al16 = al16 && ok(d.grad, d.ld_grad, 8) && ok(d.acc, d.ld_acc, 4) && ok(d.P, d.ld_state, 4) &&
+           ok(d.M, d.ld_state, 4) && ok(d.V, d.ld_state, 4) && ok(d.out, d.ld_out, 4);
+    elems += d.n * d.m;
+    rows += d.n * d.rv_cb;
+  }
+};
 
-bool use_rv(const DevMat& one, int32_t mode, bool adam, bool pack, bool g16, int64_t elems) {
+enum RmPass { kRmFused, kRmPart, kRmZen, kRmDeferred };
+
+bool rv_pays(const RmSet& s, RmPass pass) {
+  if (s.al16) return true;
+  if (pass == kRmDeferred) return s.elems >= (int64_t(1) << 22) && s.elems >= 128 * s.rows;
+  const int lg = pass == kRmZen ? 24 : pass == kRmFused ? 25 : 26;
+  return s.elems >= (int64_t(1) << lg) && s.elems >= 640 * s.rows;
+}
+
+bool use_rv(const DevMat& one, int32_t mode, bool adam, bool pack, const RmSet& set) {
   if (one.layout != zf::kRowMajor || !one.rv) return false;
   if (adam && mode != zf::kInplace) return false;
-  return !(adam && !pack && !g16 && elems < kSmallAdam);
+  return rv_pays(set, adam && pack ? kRmFused : kRmPart);
 }
 
 int64_t rv_grid(const DevMat& d) { return rv_blocks(d.n, d.m, d.rv_rows); }
@@ -586,7 +622,9 @@ zf_status run_update(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
                                                           as_stream(stream));
     return e == hipSuccess ? ZF_OK : hip_fail(e);
   }
-  const bool rv = use_rv(d, mode, adam, pack, d.vec != 0, n * m);
+  RmSet set;
+  set.add(d);
+  const bool rv = use_rv(d, mode, adam, pack, set);
   const int64_t blocks = rv ? rv_grid(d) : update_grid(d);
   if (blocks == 0) return ZF_OK;
   const hipError_t e = launch_update_any(single_table(d), d, blocks, c, adam ? mode : 0,
@@ -881,8 +919,8 @@ struct zf_plan {
   double* d_zb = nullptr;  // Zen-auto per-finalize-block sums
   int64_t blk_cn = 0, blk_fin = 0, blk_top = 0, blk_up = 0, blk_unp = 0, blk_zen = 0, blk_zp = 0,
           blk_upv = 0, blk_sel = 0;
-  int64_t k_total = 0, u_total = 0, elems = 0;
-  bool g16 = true;  // row-major: every gradient has 16-byte rows
+  int64_t k_total = 0, u_total = 0;
+  RmSet set;  // row-major: what the choice of the update kernel looks at
   bool ragged = false;  // channel-major: some matrix is off the aligned vector path
   bool can_colnorm = true, can_topk = true, can_adam = true, can_remap = true, can_pack = true,
        can_unpack = true, can_zen = true, can_scatter = true, can_handover = true,
@@ -1073,8 +1111,7 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
     }
     p->k_total += d.k;
     p->u_total += d.m - d.k;
-    p->elems += d.n * d.m;
-    p->g16 = p->g16 && d.vec != 0;
+    p->set.add(d);
     p->ragged = p->ragged || is_ragged(d);
     off_cn[q] = p->blk_cn;
     off_fin[q] = p->blk_fin;
@@ -1269,7 +1306,7 @@ hipError_t plan_update_launch(const zf_plan* p, const AdamK& c, int32_t mode, in
     const Table ts{p->d_mats, p->d_off_sel, p->nmats, p->ragged};
     return zf::launch_cm_adam_selected_grid(ts, p->mats[0], p->blk_sel, c, mode, s);
   }
-  const bool rv = use_rv(p->mats[0], mode, adam, pack, p->g16, p->elems);
+  const bool rv = use_rv(p->mats[0], mode, adam, pack, p->set);
   const Table t{p->d_mats, rv ? p->d_off_upv : p->d_off_up, p->nmats, p->ragged};
   return launch_update_any(t, p->mats[0], rv ? p->blk_upv : p->blk_up, c, adam ? mode : 0, first,
                            adam, pack, p->layout, s, handover, scale, rv);
@@ -1412,9 +1449,9 @@ zf_status zf_plan_update_handover_deferred(zf_plan* p, const zf_adam_hparams* hp
   if (!hparams_ok(hp) || step < 1 || !std::isfinite(scale)) return ZF_EINVAL;
   if (earlier == nullptr || n_earlier < 1) return ZF_EINVAL;
   const bool cm = p->layout == zf::kChannelMajor;
-  // row-major: the 16-byte kernel reads the earlier gradients as it reads
-  // this step's (16-byte rows, strides within its 32-bit row offsets)
-  bool rv = !cm && p->mats[0].rv;
+  // row-major: the 16-byte hand-over reads the earlier gradients as it reads
+  // this step's (rows of any alignment, strides within its 32-bit row offsets)
+  bool rv = !cm && p->mats[0].rv && rv_pays(p->set, kRmDeferred);
   zf::HistTable h{};
   const zf_status st = gather_earlier(p, earlier, n_earlier, h, rv);
   if (st != ZF_OK) return st;
@@ -1424,15 +1461,14 @@ zf_status zf_plan_update_handover_deferred(zf_plan* p, const zf_adam_hparams* hp
   if (cm) {
     e = zf::launch_cm_handover_deferred(Table{p->d_mats, p->d_off_up, p->nmats, p->ragged}, p->mats[0],
                                         p->blk_up, c, scale, h, stm);
-  } else if (rv) {
-    e = zf::launch_rv_handover_deferred(Table{p->d_mats, p->d_off_upv, p->nmats, p->ragged}, p->mats[0],
-                                        p->blk_upv, c, scale, h, stm);
   } else {
-    e = zf::launch_update(Table{p->d_mats, p->d_off_up, p->nmats, p->ragged}, p->mats[0], p->blk_up, c,
-                          zf::kInplace, 0, true, false, false, 1.0f, stm);
-    if (e == hipSuccess)
-      e = zf::launch_rm_handover_deferred(Table{p->d_mats, p->d_off_unp, p->nmats, p->ragged}, p->blk_unp,
-                                          scale, h, stm);
+    e = plan_update_launch(p, c, zf::kInplace, 0, true, false, false, 1.0f, stm);
+    if (e == hipSuccess && rv)
+      e = zf::launch_rv_handover_deferred(Table{p->d_mats, p->d_off_upv, p->nmats, p->ragged},
+                                          p->mats[0], p->blk_upv, scale, h, stm);
+    else if (e == hipSuccess)
+      e = zf::launch_rm_handover_deferred(Table{p->d_mats, p->d_off_unp, p->nmats, p->ragged},
+                                          p->blk_unp, scale, h, stm);
   }
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -1488,7 +1524,9 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
   // force_end 2: the interval ends here and the update writes the hand-over
   // where it can (channel-major; row-major steps in place on the 16-byte
   // update); elsewhere a plain end, the hand-over left to the gated pass
-  const bool rv = p->layout == zf::kRowMajor && pd == nullptr && use_rv(p->mats[0], mode, true, true, p->g16, p->elems);
+  const bool vec = p->layout == zf::kRowMajor && pd == nullptr && p->mats[0].rv &&
+                   rv_pays(p->set, kRmZen);
+  const bool rv = vec && mode == zf::kInplace;
   const bool fuse = force_end == 2 && p->can_handover && zst != nullptr &&
                     (p->layout == zf::kChannelMajor || rv);
   if (force_end == 2 && !fuse) force_end = 1;
@@ -1505,7 +1543,7 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
     if (e != hipSuccess) return hip_fail(e);
     const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
     e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
-  } else if (p->mats[0].rv && pd == nullptr) {
+  } else if (vec) {
     // A refresh on 16-byte buffers: Adam alone in the per-column kernel (first:
     // it reads what the caller gives as state sources, the packing writes),
     // then the packing with the statistics in the 16-byte one, instead of both

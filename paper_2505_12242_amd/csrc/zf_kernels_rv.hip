@@ -585,15 +585,12 @@ hipError_t launch_rv_update(const Table& t, const DevMat& one, int64_t blocks, c
 }
 
 hipError_t launch_rv_handover_deferred(const Table& t, const DevMat& one, int64_t blocks,
-                                       const AdamK& c, float scale, const HistTable& h,
-                                       hipStream_t s) {
+                                       float scale, const HistTable& h, hipStream_t s) {
   (void)hipGetLastError();
   if (blocks <= 0 || t.mats == nullptr) return hipSuccess;
-  launch_rv_a<true, false, false, false, 0>(t, one, dim3(static_cast<uint32_t>(blocks)), c, 0,
-                                                1.0f, s, nullptr);
   hipLaunchKernelGGL((rv_update_kernel<true, false, false, false, false, 0, true>),
                      dim3(static_cast<uint32_t>(blocks)), dim3(kThreads), 0, s, t.mats, t.off,
-                     t.nmats, one, c, 0, scale, nullptr, h, nullptr);
+                     t.nmats, one, AdamK{}, 0, scale, nullptr, h, nullptr);
   return hipGetLastError();
 }
 

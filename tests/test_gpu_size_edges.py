@@ -122,9 +122,69 @@ def test_row_major_zen_against_channel_major(n, m):
                 assert rel_close(b, a, 2.0 ** -22)[0], (form, n, m, t)
 
 
+# Row-major sets that are wide and large enough for the 16-byte update although
+# no buffer has 16-byte rows (2^26 elements, tiles of 640 columns or more),
+# against the same data in 16-byte rows: identical bits in every pass.  Columns
+# at the edges of a tile, of an 8-column group and of a tile's slot quads, a last
+# row block of a few rows.
+@pytest.mark.parametrize("m", [641, 1000, 1921, 4001])
+def test_row_major_large_sets_in_rows_of_any_alignment(m):
+    n = -(-(1 << 26) // m)
+    dev, hp, k = torch.device("cuda"), zf.AdamHparams(lr=1e-3, weight_decay=0.01), zf.k_from_ratio(0.1, m)
+    gen = torch.Generator(device=dev).manual_seed(m)
+
+    def buf(dtype, cols, aligned):
+        if aligned:
+            return zf.alloc_stored(zf.ROW_MAJOR, n, cols, dtype)
+        return torch.empty(n * (cols + 1 + cols % 2) + 1, dtype=dtype, device=dev)[1:].view(
+            n, cols + 1 + cols % 2)[:, :cols]
+
+    def twins(dtype, cols, scale=1.0, fill=None):
+        src = (torch.randn(n, cols, generator=gen, device=dev) * scale if fill is None
+               else torch.full((n, cols), fill, device=dev))
+        return [buf(dtype, cols, al).copy_(src) for al in (True, False)]
+
+    sel = zf.topk_select(torch.rand(m, generator=gen, device=dev), 0.1)
+    G = [twins(torch.bfloat16, m) for _ in range(3)]
+    W = twins(torch.bfloat16, m, 0.02)
+    st = [twins(torch.float32, k, 0.02), twins(torch.float32, k, 1e-3), twins(torch.float32, k, fill=1e-4)]
+    acc, out = twins(torch.float32, m - k, fill=0.0), twins(torch.float32, m, fill=0.0)
+    stage = [zf.alloc_stored(zf.ROW_MAJOR, n, m, torch.bfloat16).zero_() for _ in range(2)]
+    sq = [(torch.zeros(k, device=dev), torch.zeros(m - k, device=dev)) for _ in range(2)]
+    totals = [torch.zeros(zf.ZEN_TOTALS_BYTES // 8, dtype=torch.int64, device=dev) for _ in range(2)]
+    plans = []
+    for a in range(2):
+        kw = dict(k=k, sel=sel, weight=W[a], master=st[0][a], exp_avg=st[1][a],
+                  exp_avg_sq=st[2][a], acc=acc[a], unpacked=out[a], layout=zf.ROW_MAJOR)
+        plans.append(([zf.Plan([zf.MatrixBuffers(grad=g[a], **kw)]) for g in G],
+                      [zf.Plan([zf.MatrixBuffers(grad=g[a], acc_first=stage[a], **kw)]) for g in G],
+                      zf.Plan([zf.MatrixBuffers(grad=G[0][a], sel_sq=sq[a][0], acc_sq=sq[a][1], **kw)])))
+    I = zf.STATES_INPLACE
+    calls = [("first", lambda a, P, S, Z: P[0].update(hp, 1, I, 1, 4)),
+             ("later", lambda a, P, S, Z: P[1].update(hp, 2, I, 2, 4)),
+             ("hand-over", lambda a, P, S, Z: P[2].update_handover(hp, 3, I, 3, 3, 1 / 3)),
+             ("first, stage", lambda a, P, S, Z: S[0].update(hp, 4, I, 1, 4)),
+             ("second, stage", lambda a, P, S, Z: S[1].update(hp, 5, I, 2, 4)),
+             ("second, stage, hand-over", lambda a, P, S, Z: S[1].update_handover(hp, 6, I, 2, 2, 0.5)),
+             ("Adam", lambda a, P, S, Z: P[1].update(hp, 7, I, 1, 4, pack=False)),
+             ("packing", lambda a, P, S, Z: P[2].update(hp, 8, I, 2, 4, adam=False)),
+             ("deferred", lambda a, P, S, Z: P[2].update_handover_deferred(hp, 9, P[:2], 0.25)),
+             ("Zen-auto", lambda a, P, S, Z: Z.update_zen(hp, 10, I, 2, 4, 1.0, totals[a]))]
+    for name, call in calls:
+        for a in range(2):
+            call(a, *plans[a])
+        torch.cuda.synchronize()
+        for i, (x, y) in enumerate([W, *st, acc, out, stage, totals, *zip(*sq)]):
+            it = torch.int16 if x.dtype == torch.bfloat16 else torch.int32 if x.dtype == torch.float32 else x.dtype
+            assert torch.equal(x.view(it), y.view(it)), (name, i)
+    for P, S, Z in plans:
+        for p in (*P, *S, Z):
+            p.close()
+
+
 # The runner on rows of any alignment, bit for bit against the oracle.
-# Row-major: gradient rows of an odd number of elements through the 16-byte
-# kernel (all phases, with and without the bf16 stage, the deferred hand-over).
+# Row-major: gradient rows of an odd number of elements (all phases, with and
+# without the bf16 stage, the deferred hand-over).
 # Channel-major: channels of n % 8 != 0 through the ragged kernels, n at the
 # edges of a quad, a lane's quads and a chunk, next to an aligned matrix.
 def _odd_runner(layout, shapes, how):

@@ -30,8 +30,8 @@ class Recorder:
         self.rec = ctypes.CDLL(os.environ["ZF_RECORDER"])
         self.buf = ctypes.create_string_buffer(1 << 16)
         self.hp = _lib.ZfAdamHparams(1e-5, 0.9, 0.999, 1e-8, 0.0)
-        self.top = 0x7F0000000000
-        self.state = self.addr(64, 0)
+        self.top = 0x100000000000
+        self.state = self.addr(8192, 0)
         self.names = {}
 
     def addr(self, nbytes, off):
@@ -111,6 +111,21 @@ class Recorder:
         return self.call("zf_plan_update", p, ctypes.byref(self.hp), 5, mode, sii, 8, adam, pack,
                          None)
 
+    def zen(self, p, mode=INPLACE, force=0):
+        return self.call("zf_plan_update_zen_device", p, ctypes.byref(self.hp), 5, mode, 8, force,
+                         1.0, self.state, self.state + 4096, None)
+
+    def fused(self, x, mode=INPLACE):
+        return self.call("zf_update_fused", x.grad, x.n, x.m, x.ld_grad, x.layout,
+                         ctypes.byref(x.sel), x.k, x.master, x.exp_avg, x.exp_avg_sq, x.ld_state,
+                         x.weight, x.ld_weight, ctypes.byref(self.hp), 5, mode, None, x.acc,
+                         x.ld_acc, 2, 4, None)
+
+    def adam(self, x, mode=INPLACE):
+        return self.call("zf_adam_selected", x.grad, x.n, x.m, x.ld_grad, x.layout,
+                         ctypes.byref(x.sel), x.k, x.master, x.exp_avg, x.exp_avg_sq, x.ld_state,
+                         x.weight, x.ld_weight, ctypes.byref(self.hp), 5, mode, None, None)
+
     def deferred(self, p, earlier):
         hs = (ctypes.c_void_p * len(earlier))(*[e.value for e in earlier])
         return self.call("zf_plan_update_handover_deferred", p, ctypes.byref(self.hp), 5, hs,
@@ -131,8 +146,36 @@ def scenarios(r):
                 p = r.plan(a)
                 out[f"no-grad {layout} {off} {ratio}"] = [r.deferred(p, [r.plan(e)]),
                                                           r.deferred(p, [r.plan(none)])]
+    # row-major routes by alignment, width and size
+    for name, shapes, kw in ROW_MAJOR_SETS:
+        mats = [r.matrix(n, m, RM, zen=True, **kw) for n, m in shapes]
+        p, e = r.plan(mats), r.plan([r.matrix(n, m, RM, **kw) for n, m in shapes])
+        out["rm " + name] = {
+            "fused": r.update(p), "init": r.update(p, INIT), "adam": r.update(p, pack=0),
+            "pack": r.update(p, adam=0), "deferred": r.deferred(e, [e]), "zen": r.zen(p),
+            "zen-init": r.zen(p, INIT), "zen-end": r.zen(p, force=2),
+            "call-fused": r.fused(mats[0]), "call-adam": r.adam(mats[0])}
     return out
 
+
+# name, shapes, and how their buffers lie (off16 / off32: bytes past a 16-byte
+# boundary, rows then unpadded)
+ROW_MAJOR_SETS = [
+    ("aligned small", [(64, 72)], {}),
+    ("aligned narrow", [(50000, 32)], {}),
+    ("odd rows, small", [(1024, 1023)] * 8, {"off16": 2}),
+    ("odd rows, five small", [(1024, 1024)] * 4 + [(1024, 1023)], {"off16": 2}),
+    ("odd states, small", [(1024, 1024)], {"off32": 4}),
+    ("odd rows, narrow", [(1 << 20, 33)], {"off16": 2}),
+    ("odd rows, tiles of 512", [(65600, 1023)], {"off16": 2}),
+    ("odd rows, 2^22 wide", [(1049, 4001)], {"off16": 2}),
+    ("odd rows, 2^24 wide", [(4194, 4001)], {"off16": 2}),
+    ("odd rows, 2^25 wide", [(8387, 4001)], {"off16": 2}),
+    ("odd rows, 2^25 wide over 8", [(1049, 4001)] * 8, {"off16": 2}),
+    ("odd rows, 2^26 wide", [(16774, 4001)], {"off16": 2}),
+    # a weight whose row stride is too long for the statistics' row blocks
+    ("long rows", [(64, 72)], {"ld": 1 << 26}),
+]
 
 if __name__ == "__main__":
     print("RESULT " + json.dumps(scenarios(Recorder())))
@@ -173,3 +216,49 @@ def test_deferred_handover_needs_the_earlier_gradients(routes, off, ratio):
     with_grad, without = routes[f"no-grad {CM} {off} {ratio}"]
     assert with_grad[0] == 0 and len(with_grad[1]) == 1
     assert without[0] == (0 if ratio == 1.0 else EINVAL)
+
+
+COL, VEC = "update_kernel", "rv_update_kernel"
+# the passes in which each set takes the 16-byte kernel
+ROW_MAJOR_VEC = {
+    "aligned small": {"fused", "adam", "pack", "deferred", "zen", "call-fused", "call-adam"},
+    "aligned narrow": {"fused", "adam", "pack", "deferred", "zen", "call-fused", "call-adam"},
+    "odd rows, small": {"deferred"},  # (8 M elements: the hand-over alone)
+    "odd rows, five small": {"deferred"},
+    "odd states, small": set(),
+    "odd rows, narrow": set(),
+    "odd rows, tiles of 512": {"deferred"},
+    "odd rows, 2^22 wide": {"deferred"},
+    "odd rows, 2^24 wide": {"deferred", "zen"},
+    "odd rows, 2^25 wide": {"fused", "deferred", "zen", "call-fused"},
+    "odd rows, 2^25 wide over 8": {"fused", "deferred", "zen"},
+    "odd rows, 2^26 wide": {"fused", "adam", "pack", "deferred", "zen", "call-fused", "call-adam"},
+    # (its plan with the Zen-auto statistics has blocks of 16 rows or more;
+    # without them, and in the calls, 4 rows fit)
+    "long rows": {"deferred", "call-fused", "call-adam"},
+}
+
+
+@pytest.mark.parametrize("name", list(ROW_MAJOR_VEC))
+def test_row_major_routes(routes, name):
+    """In place, packing alone and the hand-over: the 16-byte kernel where every
+    buffer has 16-byte rows, or where the set is wide and large; a refresh: the
+    per-column kernel; long rows: the per-column kernels."""
+    got, vec = routes["rm " + name], ROW_MAJOR_VEC[name]
+
+    def kernels(what):
+        status, launches = got[what]
+        assert status == 0, what
+        return [x[0].split("<")[0] for x in launches]
+
+    for what in ("fused", "adam", "pack", "call-fused", "call-adam"):
+        assert kernels(what) == [VEC if what in vec else COL], what
+    assert kernels("init") == [COL]
+    adam = VEC if "adam" in vec or name == "long rows" else COL
+    assert kernels("deferred") == [adam, VEC if "deferred" in vec else "rm_handover_deferred_kernel"]
+    tail = ["rm_zen_finalize_kernel", "zen_total_kernel"]
+    partial = ["rm_zen_partial_kernel"]
+    zen = "zen" in vec
+    assert kernels("zen") == ([VEC] if zen else [COL] + partial) + tail
+    assert kernels("zen-end") == ([VEC] if zen else [COL] + partial) + tail
+    assert kernels("zen-init") == ([COL, VEC] if zen else [COL] + partial) + tail
