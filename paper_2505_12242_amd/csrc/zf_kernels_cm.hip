@@ -19,7 +19,8 @@
 // n % 8 == 0 and 16-byte aligned rows (DevMat::vec).  Other shapes (RAG
 // kernels, launched where the table holds one) take the same quads through
 // accesses of 2-byte (bf16) and 4-byte (fp32) alignment, and the up to three
-// rows after a channel's last whole quad element by element.  Measured on a
+// rows after a channel's last whole quad element by element; short channels
+// (DevMat::cm_quads unset) all of them.  Measured on a
 // 5003 x 3001 weight against one element per lane and access: scores 37.4 -> 8.3
 // us, fused first step 44 -> 27, fused hand-over 44 -> 33.
 #include <type_traits>
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
   const rsrc_t rS = st ? make_rsrc(d.acc1 + j * d.ld_acc1, n * 2) : r;
   // the rows of whole 16-byte groups; RAG: the rest element by element below
   const bool rag = RAG && !d.vec;
-  const int64_t n8 = rag ? n & ~int64_t(7) : n;
+  const int64_t n8 = rag ? (d.cm_quads ? n & ~int64_t(7) : 0) : n;
   const rsrc_t rO = OUT == 2 ? make_rsrc(d.out + j * d.ld_out, n8 * 4) : r;
   const uint16_t* __restrict__ pg = d.grad + j * d.ld_grad;
   uint16_t* __restrict__ ps = st ? d.acc1 + j * d.ld_acc1 : nullptr;
@@ -268,11 +269,11 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
     }
   }
   if constexpr (RAG) {
-    if (n8 + lane < n) {  // at most seven rows
-      const uint16_t gb = pg[n8 + lane];
-      if (st) ps[n8 + lane] = gb;
+    for (int64_t e = n8 + lane; e < n; e += 64) {
+      const uint16_t gb = pg[e];
+      if (st) ps[e] = gb;
       const float g = widen_bf16(gb);
-      if constexpr (OUT == 2) d.out[j * d.ld_out + n8 + lane] = g * scale;
+      if constexpr (OUT == 2) d.out[j * d.ld_out + e] = g * scale;
       const double x = static_cast<double>(g);
       a0 = __builtin_fma(x, x, a0);
     }
@@ -469,15 +470,16 @@ __device__ __forceinline__ void cm_pack_piece(int qpt, const Row16& rG, rsrc_t r
 }
 
 // fn(path, e0, len) over the pieces of rows [e0, e0 + len): the whole of them on
-// the vector path; RAG kernels, off it: the whole quads, then the rest.
+// the vector path; RAG kernels, off it: the whole quads (of matrices that take
+// them: cm_quads), then the rest.
 template <bool RAG, typename Fn>
-__device__ __forceinline__ void cm_pieces(bool vec, int64_t e0, int64_t len, Fn fn) {
+__device__ __forceinline__ void cm_pieces(const DevMat& d, int64_t e0, int64_t len, Fn fn) {
   if constexpr (!RAG) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
-  } else if (vec) {
+  } else if (d.vec) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
   } else {
-    const int64_t n4 = len & ~int64_t(3);
+    const int64_t n4 = d.cm_quads ? len & ~int64_t(3) : 0;
     if (n4 > 0) fn(std::integral_constant<int, kPathRag>{}, e0, n4);
     if (len > n4) fn(std::integral_constant<int, kPathElem>{}, e0 + n4, len - n4);
   }
@@ -714,7 +716,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
   double ss = 0.0;
 
   if (!sel) {
-    cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       if (mode == kRemap && d.st_P != nullptr) cm_swap_out<P>(d, j, w, e0, len);
@@ -749,7 +751,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
       }
     });
   } else if constexpr (ADAM) {
-    cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
@@ -834,7 +836,7 @@ __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
   const uint64_t mj = uniform_u64(d.mask[j >> 6]);
   const bool sel = (mj >> (j & 63)) & 1ull;
   double ss = 0.0;
-  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+  cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
     constexpr int P = decltype(path)::value;
     const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
     const rsrc_t rOut = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
@@ -871,7 +873,7 @@ __device__ __forceinline__ void cm_unpack_rows(const DevMat& d, int64_t j, int64
   const int64_t u = j - (static_cast<int64_t>(uniform_i32(d.prefix[w])) +
                          __popcll(mw & ((uint64_t(1) << (j & 63)) - 1)));
   const int tid = threadIdx.x;
-  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+  cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
     constexpr int P = decltype(path)::value;
     const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
     if (sel) {
@@ -914,7 +916,7 @@ __device__ __forceinline__ void cm_handover_rows_deferred(const DevMat& d, int32
   const uint64_t mw = uniform_u64(d.mask[j >> 6]);
   const bool sel = (mw >> (j & 63)) & 1ull;
   double ss = 0.0;  // (no statistics)
-  cm_pieces<RAG>(d.vec, e0, len, [&](auto path, int64_t e0, int64_t len) {
+  cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
     constexpr int P = decltype(path)::value;
     const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
     const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);

@@ -186,7 +186,8 @@ def test_row_major_large_sets_in_rows_of_any_alignment(m):
 # Row-major: gradient rows of an odd number of elements (all phases, with and
 # without the bf16 stage, the deferred hand-over).
 # Channel-major: channels of n % 8 != 0 through the ragged kernels, n at the
-# edges of a quad, a lane's quads and a chunk, next to an aligned matrix.
+# edges of a quad, a lane's quads, a chunk and the shortest channels that take
+# quads (1000 rows), next to an aligned matrix and to a long odd one.
 def _odd_runner(layout, shapes, how):
     cm = layout == zf.CHANNEL_MAJOR
     R, S, T = 8, 4, 9
@@ -227,15 +228,15 @@ def test_row_major_odd_rows_runner(shape, how):
     _odd_runner(zf.ROW_MAJOR, [shape], how)
 
 
-@pytest.mark.parametrize("n", [1, 3, 5, 255, 1027, 2047, 2049, 4099])
+@pytest.mark.parametrize("n", [1, 3, 5, 255, 999, 1001, 1027, 2047, 2049, 4099])
 @pytest.mark.parametrize("how", ["stage", "plain", "separate", "deferred"])
 def test_channel_major_odd_channels_runner(n, how):
-    _odd_runner(zf.CHANNEL_MAJOR, [(n, 21), (64, 10)], how)
+    _odd_runner(zf.CHANNEL_MAJOR, [(n, 21), (64, 10), (1003, 5)], how)
 
 
-# Channel-major scores of channels of any length: whole groups of eight, the
-# rows after them, and both stores a refresh may ride on the pass.
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 511, 513, 2048, 2055, 4099])
+# Channel-major scores of channels of any length: element by element below 1000
+# rows, else whole groups of eight and the rows after them, and both stores a refresh may ride on the pass.
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 511, 513, 999, 1001, 2048, 2055, 4099])
 def test_channel_major_odd_scores(n):
     m, dev = 13, torch.device("cuda")
     g = gbits(n, m, n)
