@@ -1447,6 +1447,22 @@ zf_status gather_earlier(const zf_plan* p, const zf_plan* const* earlier, int32_
   return ZF_OK;
 }
 
+// Channel-major with deferred packing: whether a hand-over keeps kCmSumDeep
+// kept gradients in flight instead of kCmSumBatch.  They take 94 to 103
+// registers a lane instead of 61 to 68, so 4 to 5 waves fit a SIMD instead of 7
+// to 8: short channels, whose waves hold few bytes each, lose.  Hand-over of a
+// fixed interval of 4 steps, 4 / 8 in flight, in us: 64 rows a block (100000
+// channels) 161 / 208, 256 58 / 72, 1024 27 / 30, 1706 (13B layer) 769 / 745, 4000
+// (7B layer) 418 / 408, 70B layer 2120 / 2085; of 8 steps, 70B layer 3221 / 3169.
+// The gated hand-over has the registers of two chunks a lane, so there eight
+// pay only where there are more than four steps to add: 4 steps, 7B set
+// 12.5 / 12.8 ms, 8 steps 19.1 / 16.9.
+constexpr int64_t kDeepRows = 1536;  // of a block, on average
+
+bool cm_deep(const zf_plan* p, int32_t n_earlier, bool gated) {
+  return p->set.elems >= kDeepRows * p->blk_up && (!gated || n_earlier + 1 > zf::kCmSumBatch);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1469,7 +1485,7 @@ zf_status zf_plan_update_handover_deferred(zf_plan* p, const zf_adam_hparams* hp
   hipError_t e;
   if (cm) {
     e = zf::launch_cm_handover_deferred(Table{p->d_mats, p->d_off_up, p->nmats, p->ragged}, p->mats[0],
-                                        p->blk_up, c, scale, h, stm);
+                                        p->blk_up, c, scale, h, cm_deep(p, n_earlier, false), stm);
   } else {
     e = plan_update_launch(p, c, zf::kInplace, 0, true, false, false, 1.0f, stm);
     if (e == hipSuccess && rv)
@@ -1692,7 +1708,7 @@ zf_status zf_plan_handover_zen_deferred(zf_plan* p, const zf_plan* const* earlie
   if (st != ZF_OK) return st;
   const hipError_t e = zf::launch_cm_unpack_zen_deferred(
       Table{p->d_mats, p->d_off_unp, p->nmats, p->ragged}, p->blk_unp, h,
-      reinterpret_cast<const zf::ZenState*>(state), as_stream(stream));
+      cm_deep(p, n_earlier, true), reinterpret_cast<const zf::ZenState*>(state), as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
 

@@ -74,7 +74,11 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 //   Adam, selected grid  13B layer (79 K) 457 / 451 / 469, 70B (84 K) 450 / 436 /
 //                        440, 12 7B layers (265 K) 1405 / 1383 / 1381, 20 (430 K)
 //                        2273 / 2240 / 2222
-// (runs of 16 are within 2% of 64; 1024 lose the balance).
+// (runs of 16 are within 2% of 64; 1024 lose the balance).  What decides is the
+// size of the pass, `work`: the grid's blocks, or what a smaller grid of larger
+// blocks walks: row-major blocks count their rows in sixteens (Zen-auto's blocks
+// of 256 rows on the 7B set, 30 K of them, RUN 64 / one range: 19.5 / 19.0 ms),
+// the gated hand-over's fixed grid its units (8.7 / 8.3 ms).
 #ifndef ZF_XCD_REMAP
 #define ZF_XCD_REMAP 1
 #endif
@@ -83,13 +87,13 @@ constexpr uint32_t kXcds = 8;
 enum XcdOrder { kOrderScores, kOrderStream, kOrderSelected, kOrderRowMajor };
 
 template <int ORDER = kOrderStream>
-__device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B) {
+__device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B, int64_t work) {
   if constexpr (ZF_XCD_REMAP == 0) return b;
   uint32_t lg;  // log2 RUN, or 0: one range per XCD
-  if constexpr (ORDER == kOrderScores) lg = B <= (1u << 17) ? 6 : 0;
-  else if constexpr (ORDER == kOrderRowMajor) lg = B <= (1u << 17) ? 6 : 0;
-  else if constexpr (ORDER == kOrderSelected) lg = B <= (1u << 18) ? 8 : 0;
-  else lg = B <= (1u << 17) ? 6 : B <= (1u << 20) ? 8 : 0;
+  if constexpr (ORDER == kOrderScores) lg = work <= (1 << 17) ? 6 : 0;
+  else if constexpr (ORDER == kOrderRowMajor) lg = work <= (1 << 17) ? 6 : 0;
+  else if constexpr (ORDER == kOrderSelected) lg = work <= (1 << 18) ? 8 : 0;
+  else lg = work <= (1 << 17) ? 6 : work <= (1 << 20) ? 8 : 0;
   const uint32_t full = lg != 0 ? B >> (lg + 3) << (lg + 3) : 0;
   if (b < full) {
     const uint32_t i = b & ((kXcds << lg) - 1);
@@ -101,6 +105,11 @@ __device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B) {
   return full + (x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i);
 }
 
+template <int ORDER = kOrderStream>
+__device__ __forceinline__ int64_t xcd_remap(uint32_t b, uint32_t B) {
+  return xcd_remap<ORDER>(b, B, B);
+}
+
 // Descriptor of the matrix the (remapped) block belongs to.  BATCHED kernels
 // read it from the plan's device table (scalar loads); single-matrix kernels
 // take it by value.  Keeping the two apart avoids a generic pointer that
@@ -110,7 +119,10 @@ __device__ __forceinline__ const DevMat& get_mat(const DevMat* __restrict__ mats
                                                  const int64_t* __restrict__ off, int32_t nmats,
                                                  const DevMat& one, int64_t& local,
                                                  int32_t& index) {
-  const int64_t b = xcd_remap<ORDER>(blockIdx.x, gridDim.x);
+  int64_t work = gridDim.x;
+  if constexpr (ORDER == kOrderRowMajor)  // (blocks of 8 rows, on small grids, count as 16)
+    work *= max(1, (BATCHED ? mats[0].rv_rows : one.rv_rows) / 16);
+  const int64_t b = xcd_remap<ORDER>(blockIdx.x, gridDim.x, work);
   if constexpr (!BATCHED) {
     local = b;
     index = 0;

@@ -47,6 +47,8 @@ constexpr int kCmUnpackQpt = ZF_CM_UNPACK_QPT;
 constexpr int kCmUnpackChunk = kThreads * 4 * kCmUnpackQpt;
 constexpr int kCmSelChunk = kThreads * 4;  // rows per block of the selected-only Adam grid
 constexpr int kCmColnormCols = kThreads / 64;
+constexpr int kCmSumBatch = 4;  // kept gradients loaded before they are added (see cm_deep)
+constexpr int kCmSumDeep = 8;
 constexpr int kCmWaves = kThreads / 64;  // waves per update block (one statistics partial each)
 
 // Zen-auto: channels per finalize block (channel-major; row-major kFinCols)
@@ -238,8 +240,9 @@ hipError_t launch_cm_unpack_zen(const Table& t, const DevMat& one, int64_t units
 // `out`; at the unselected channels out = scale * (((g_1 + g_2) + ...) + g),
 // g_s the channel's row of the gradient of earlier step s (h.mats[s - 1]),
 // g this step's.
+// deep: kCmSumDeep of the gradients in flight, else kCmSumBatch.
 hipError_t launch_cm_handover_deferred(const Table& t, const DevMat& one, int64_t blocks,
-                                       const AdamK& c, float scale, const HistTable& h,
+                                       const AdamK& c, float scale, const HistTable& h, bool deep,
                                        hipStream_t s);
 // Zen-auto on the device with deferred packing (channel-major): the update
 // with the statistics of the interval's running sum taken from the kept
@@ -251,7 +254,7 @@ hipError_t launch_cm_update_zen_deferred(const Table& t, const DevMat& one, int6
 // Its gated hand-over (ended == 1): the interval's sums from the kept
 // gradients and the plan's own (unpack table and units).
 hipError_t launch_cm_unpack_zen_deferred(const Table& t, int64_t units, const HistTable& h,
-                                         const ZenState* zst, hipStream_t s);
+                                         bool deep, const ZenState* zst, hipStream_t s);
 // from_stage: the source is the bf16 first-step stage (a one-step interval;
 // every matrix of the table has one).
 hipError_t launch_cm_unpack(const Table& t, const DevMat& one, int64_t blocks, float scale,

@@ -538,23 +538,18 @@ __device__ __forceinline__ void cm_swap_out(const DevMat& d, int64_t j, int64_t 
 // added in step order in fp32 (the accumulation's own sequence, so the
 // same bits as packing every step).  STATS: ss += the squares of the sums,
 // in fp64; WRITE: scale times the sums to rOut.
-template <int QPT, bool STATS, bool WRITE, bool RAG>
+template <int QPT, bool STATS, bool WRITE, bool RAG, int BATCH>
 __device__ __forceinline__ void cm_interval_sum_vec(const HistTable& h, int32_t s_first, int32_t q,
                                                     int64_t j, int64_t e0, int64_t len,
                                                     const Row16& rG, rsrc_t rOut, float scale,
                                                     double& ss) {
   const int tid = threadIdx.x;
-  // steps whose rows are loaded before they are added: 8 against 4, hand-over
-  // of a Llama-2-70B layer (8 steps) 3221 -> 3169 us, of a 7B layer (4 steps, the
-  // loop then runs once) 422 -> 410; 2 measured as 4.  With the statistics 4: a
-  // Zen-auto period of a 7B layer 1261 us against 1283 with 8.
-  constexpr int kBatch = STATS ? 4 : 8;
   float a[QPT][kQuad];
   const int32_t steps = h.n - s_first + 1;  // the kept steps, then this one
-  for (int32_t s0 = 0; s0 < steps; s0 += kBatch) {
-    u32x2 gv[kBatch][QPT];
+  for (int32_t s0 = 0; s0 < steps; s0 += BATCH) {
+    u32x2 gv[BATCH][QPT];
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
+    for (int b = 0; b < BATCH; ++b) {
       const int32_t s = s0 + b;
       if (s < steps) {
         Row16 r = rG;
@@ -567,7 +562,7 @@ __device__ __forceinline__ void cm_interval_sum_vec(const HistTable& h, int32_t 
       }
     }
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
+    for (int b = 0; b < BATCH; ++b) {
       const int32_t s = s0 + b;
       if (s < steps) {
 #pragma unroll
@@ -614,7 +609,7 @@ __device__ __forceinline__ void cm_interval_sum_elem(const HistTable& h, int32_t
   }
 }
 
-template <bool STATS, bool WRITE, int PATH>
+template <bool STATS, bool WRITE, int PATH, int BATCH>
 __device__ __forceinline__ void cm_interval_sum_piece(int qpt, const HistTable& h, int32_t s_first,
                                                       int32_t q, int64_t j, int64_t e0,
                                                       int64_t len, const Row16& rG, rsrc_t rOut,
@@ -623,10 +618,11 @@ __device__ __forceinline__ void cm_interval_sum_piece(int qpt, const HistTable& 
   if constexpr (PATH == kPathElem)
     cm_interval_sum_elem<STATS, WRITE>(h, s_first, q, j, e0, len, rG.r, rOut, scale, ss);
   else if (qpt >= kCmQpt)
-    cm_interval_sum_vec<kCmQpt, STATS, WRITE, RAG>(h, s_first, q, j, e0, len, rG, rOut, scale, ss);
+    cm_interval_sum_vec<kCmQpt, STATS, WRITE, RAG, BATCH>(h, s_first, q, j, e0, len, rG, rOut,
+                                                          scale, ss);
   else
-    cm_interval_sum_vec<kCmQpt / 2, STATS, WRITE, RAG>(h, s_first, q, j, e0, len, rG, rOut, scale,
-                                                       ss);
+    cm_interval_sum_vec<kCmQpt / 2, STATS, WRITE, RAG, BATCH>(h, s_first, q, j, e0, len, rG, rOut,
+                                                              scale, ss);
 }
 
 // STATS (fused Adam + pack only): every wave also sums, in fp64, the squares
@@ -727,8 +723,8 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
         // times that sum to the hand-over.  Nothing else is written.
         const int32_t kept = min(max(pos - 1, 0), h.n);
         const rsrc_t rOut = HAND ? make_rsrc(d.out + j * d.ld_out + e0, len * 4) : rG.r;
-        cm_interval_sum_piece<true, HAND, P>(d.cm_qpt, h, h.n - kept, q, j, e0, len, rG, rOut,
-                                             scale, ss);
+        cm_interval_sum_piece<true, HAND, P, kCmSumBatch>(d.cm_qpt, h, h.n - kept, q, j, e0, len,
+                                                          rG, rOut, scale, ss);
       } else if constexpr (PACK) {
         const int64_t u = j - r;
         const rsrc_t rA = make_rsrc(d.acc + u * d.ld_acc + e0, len * 4);
@@ -815,7 +811,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
 // rows, as in the update.
 // ---------------------------------------------------------------------------
 
-template <bool RAG>
+template <bool RAG, int BATCH>
 __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, AdamK c,
     float scale, HistTable h) {
@@ -851,7 +847,8 @@ __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
                                                  len, ss);
       cm_zero_rows<P>(rOut, len);
     } else {
-      cm_interval_sum_piece<false, true, P>(d.cm_qpt, h, 0, q, j, e0, len, rG, rOut, scale, ss);
+      cm_interval_sum_piece<false, true, P, BATCH>(d.cm_qpt, h, 0, q, j, e0, len, rG, rOut, scale,
+                                                   ss);
     }
   });
 }
@@ -909,7 +906,7 @@ __device__ __forceinline__ void cm_unpack_rows(const DevMat& d, int64_t j, int64
 // The same with deferred packing: rows [e0, e0 + len) of channel j of the
 // hand-over are scale times the interval's sum, its kept steps (the last
 // `kept` entries of h) and this plan's gradient, or +0.0 when selected.
-template <int QPT, bool RAG>
+template <int QPT, bool RAG, int BATCH>
 __device__ __forceinline__ void cm_handover_rows_deferred(const DevMat& d, int32_t q, int64_t j,
                                                           int64_t e0, int64_t len, float scale,
                                                           const HistTable& h, int32_t kept) {
@@ -925,8 +922,8 @@ __device__ __forceinline__ void cm_handover_rows_deferred(const DevMat& d, int32
     else if constexpr (P == kPathElem)
       cm_interval_sum_elem<false, true>(h, h.n - kept, q, j, e0, len, rG.r, rD, scale, ss);
     else
-      cm_interval_sum_vec<QPT, false, true, P == kPathRag>(h, h.n - kept, q, j, e0, len, rG, rD,
-                                                           scale, ss);
+      cm_interval_sum_vec<QPT, false, true, P == kPathRag, BATCH>(h, h.n - kept, q, j, e0, len, rG,
+                                                                  rD, scale, ss);
   });
 }
 
@@ -961,7 +958,7 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_kernel(const DevMat* __res
 // DEFP (deferred packing): the interval's sums are taken from the kept
 // gradients of its earlier steps (the last length - 1 entries of h) and this
 // plan's gradient, as the deferred update would have written them.
-template <bool DEFP, bool RAG>
+template <bool DEFP, bool RAG, int BATCH = kCmSumBatch>
 __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* __restrict__ mats,
                                                                 const int64_t* __restrict__ off,
                                                                 int32_t nmats, int64_t units,
@@ -974,7 +971,7 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
   const int32_t kept = DEFP ? min(max(length - 1, 0), h.n) : 0;
   // each block walks one contiguous run of units, the runs in the
   // XCD-aware block order
-  const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t b = xcd_remap(blockIdx.x, gridDim.x, units);
   const int64_t per = (units + gridDim.x - 1) / gridDim.x;
   const int64_t u0 = b * per;
   const int64_t u1 = min(units, u0 + per);
@@ -995,12 +992,12 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
     const bool pair = u + 1 < u1 && (local + 1) / d.cm_unch == j;
     const int64_t len = min(static_cast<int64_t>(pair ? 2 : 1) * kCmUnpackChunk, d.n - e0);
     if (pair) {
-      if constexpr (DEFP) cm_handover_rows_deferred<2 * kCmUnpackQpt, RAG>(d, lo, j, e0, len, scale, h, kept);
+      if constexpr (DEFP) cm_handover_rows_deferred<2 * kCmUnpackQpt, RAG, BATCH>(d, lo, j, e0, len, scale, h, kept);
       else if (from_stage) cm_unpack_rows<true, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       else cm_unpack_rows<false, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       u += 2;
     } else {
-      if constexpr (DEFP) cm_handover_rows_deferred<kCmUnpackQpt, RAG>(d, lo, j, e0, len, scale, h, kept);
+      if constexpr (DEFP) cm_handover_rows_deferred<kCmUnpackQpt, RAG, BATCH>(d, lo, j, e0, len, scale, h, kept);
       else if (from_stage) cm_unpack_rows<true, kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       else cm_unpack_rows<false, kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       u += 1;
@@ -1158,19 +1155,24 @@ static void launch_cm_unpack_t(const Table& t, const DevMat& one, dim3 grid, flo
                        t.off, t.nmats, one, scale);
 }
 
+template <bool RAG, int BATCH>
+static void launch_cm_deferred_t(const Table& t, dim3 grid, const AdamK& c, float scale,
+                                 const HistTable& h, hipStream_t s) {
+  hipLaunchKernelGGL((cm_handover_deferred_kernel<RAG, BATCH>), grid, dim3(kThreads), 0, s, t.mats,
+                     t.off, t.nmats, c, scale, h);
+}
+
 hipError_t launch_cm_handover_deferred(const Table& t, const DevMat& one, int64_t blocks,
-                                       const AdamK& c, float scale, const HistTable& h,
+                                       const AdamK& c, float scale, const HistTable& h, bool deep,
                                        hipStream_t s) {
   (void)hipGetLastError();
   (void)one;
   if (blocks <= 0 || t.mats == nullptr) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  if (t.ragged)
-    hipLaunchKernelGGL(cm_handover_deferred_kernel<true>, grid, dim3(kThreads), 0, s, t.mats,
-                       t.off, t.nmats, c, scale, h);
-  else
-    hipLaunchKernelGGL(cm_handover_deferred_kernel<false>, grid, dim3(kThreads), 0, s, t.mats,
-                       t.off, t.nmats, c, scale, h);
+  if (t.ragged && deep) launch_cm_deferred_t<true, kCmSumDeep>(t, grid, c, scale, h, s);
+  else if (t.ragged) launch_cm_deferred_t<true, kCmSumBatch>(t, grid, c, scale, h, s);
+  else if (deep) launch_cm_deferred_t<false, kCmSumDeep>(t, grid, c, scale, h, s);
+  else launch_cm_deferred_t<false, kCmSumBatch>(t, grid, c, scale, h, s);
   return hipGetLastError();
 }
 
@@ -1221,17 +1223,22 @@ hipError_t launch_cm_unpack_zen(const Table& t, const DevMat& one, int64_t units
   return hipGetLastError();
 }
 
+template <bool RAG, int BATCH>
+static void launch_cm_unpack_zen_t(const Table& t, dim3 grid, int64_t units, const HistTable& h,
+                                   const ZenState* zst, hipStream_t s) {
+  hipLaunchKernelGGL((cm_unpack_zen_kernel<true, RAG, BATCH>), grid, dim3(kThreads), 0, s, t.mats,
+                     t.off, t.nmats, units, zst, 0, h);
+}
+
 hipError_t launch_cm_unpack_zen_deferred(const Table& t, int64_t units, const HistTable& h,
-                                         const ZenState* zst, hipStream_t s) {
+                                         bool deep, const ZenState* zst, hipStream_t s) {
   (void)hipGetLastError();
   if (units <= 0 || t.mats == nullptr) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(units < kCmUnpackZenGrid ? units : kCmUnpackZenGrid));
-  if (t.ragged)
-    hipLaunchKernelGGL((cm_unpack_zen_kernel<true, true>), grid, dim3(kThreads), 0, s, t.mats,
-                       t.off, t.nmats, units, zst, 0, h);
-  else
-    hipLaunchKernelGGL((cm_unpack_zen_kernel<true, false>), grid, dim3(kThreads), 0, s, t.mats,
-                       t.off, t.nmats, units, zst, 0, h);
+  if (t.ragged && deep) launch_cm_unpack_zen_t<true, kCmSumDeep>(t, grid, units, h, zst, s);
+  else if (t.ragged) launch_cm_unpack_zen_t<true, kCmSumBatch>(t, grid, units, h, zst, s);
+  else if (deep) launch_cm_unpack_zen_t<false, kCmSumDeep>(t, grid, units, h, zst, s);
+  else launch_cm_unpack_zen_t<false, kCmSumBatch>(t, grid, units, h, zst, s);
   return hipGetLastError();
 }
 

@@ -260,3 +260,41 @@ def test_channel_major_odd_scores(n):
         assert np.array_equal(bits_np(stage), g.T), (n, offset)
         assert same_bits(f32_np(out), O.widen(g).T * np.float32(0.5)), (n, offset)
         plan.close()
+
+
+# Channel-major hand-over of kept gradients, with four and with eight of them in
+# flight: intervals around both, short and long channels, on and off the aligned
+# path, fixed and gated.  The additions in step order, each one fp32 operation.
+@pytest.mark.parametrize("n", [64, 1023, 4096, 4099])
+@pytest.mark.parametrize("steps", [2, 4, 5, 8, 9, 16])
+def test_channel_major_handover_of_kept_gradients(n, steps):
+    m, k, dev, hp = 21, 2, torch.device("cuda"), zf.AdamHparams(lr=1e-3)
+    gen = torch.Generator(device=dev).manual_seed(n + steps)
+    G = [torch.randn(m, n, generator=gen, device=dev).bfloat16() for _ in range(steps)]
+    sel = zf.topk_select(torch.rand(m, generator=gen, device=dev), 0.1)
+    out = torch.empty(m, n, device=dev)
+    st = [torch.zeros(k, n, device=dev) for _ in range(3)]
+    w = torch.zeros(m, n, dtype=torch.bfloat16, device=dev)
+    plans = [zf.Plan([zf.MatrixBuffers(grad=g, k=k, sel=sel, weight=w, master=st[0], exp_avg=st[1],
+                                       exp_avg_sq=st[2], unpacked=out, layout=zf.CHANNEL_MAJOR)])
+             for g in G]
+
+    def want(kept):
+        a = G[-kept].float()
+        for g in G[steps - kept + 1:]:
+            a = a + g.float()
+        a = a * np.float32(1.0 / kept).item()
+        a[sel.sel_idx.long()] = 0.0
+        return a
+
+    out.fill_(float("nan"))
+    plans[-1].update_handover_deferred(hp, 3, plans[:-1], float(np.float32(1.0 / steps)))
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), want(steps).view(torch.int32))
+    for kept in {1, 2, steps}:
+        out.fill_(float("nan"))
+        plans[-1].handover_zen_deferred(plans[:-1], torch.tensor([kept, 1], dtype=torch.int32, device=dev))
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int32), want(kept).view(torch.int32)), kept
+    for p in plans:
+        p.close()

@@ -155,6 +155,15 @@ def scenarios(r):
             "pack": r.update(p, adam=0), "deferred": r.deferred(e, [e]), "zen": r.zen(p),
             "zen-init": r.zen(p, INIT), "zen-end": r.zen(p, force=2),
             "call-fused": r.fused(mats[0]), "call-adam": r.adam(mats[0])}
+    # channel-major hand-over of kept gradients: how many in flight
+    for n, m, off in ((1024, 40, 0), (4096, 40, 0), (1023, 40, 2), (4095, 40, 2)):
+        x = [r.matrix(n, m, CM, off16=off, zen=True)]
+        p = r.plan(x)
+        for steps in (2, 4, 5, 8):
+            hs = (ctypes.c_void_p * 16)(*[p.value] * (steps - 1))
+            out[f"kept {n} {steps}"] = [
+                r.deferred(p, [p] * (steps - 1)),
+                r.call("zf_plan_handover_zen_deferred", p, hs, steps - 1, r.state, None)]
     return out
 
 
@@ -262,3 +271,17 @@ def test_row_major_routes(routes, name):
     assert kernels("zen") == ([VEC] if zen else [COL] + partial) + tail
     assert kernels("zen-end") == ([VEC] if zen else [COL] + partial) + tail
     assert kernels("zen-init") == ([COL, VEC] if zen else [COL] + partial) + tail
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 4095, 4096])
+@pytest.mark.parametrize("steps", [2, 4, 5, 8])
+def test_channel_major_gradients_in_flight(routes, n, steps):
+    """Eight kept gradients in flight on long channels (in the gated hand-over
+    from five steps on), four otherwise."""
+    (st, fixed), (st2, gated) = routes[f"kept {n} {steps}"]
+    rag = "true" if n % 8 else "false"
+    assert st == 0 and st2 == 0
+    assert [x[0] for x in fixed] == [
+        f"cm_handover_deferred_kernel<{rag}, {8 if n > 2048 else 4}>"]
+    assert [x[0] for x in gated] == [
+        f"cm_unpack_zen_kernel<true, {rag}, {8 if n > 2048 and steps > 4 else 4}>"]
