@@ -436,7 +436,8 @@ void set_rv(DevMat& d, int rows, bool allow) {
 // a second one: 8 M elements, elements / quads, in us: scores 63 rows 24 / 56,
 // 511 9.5 / 12, 1023 8.9 / 8.5, 4095 12 / 7; later step 159 / 270, 42 / 49, 34 /
 // 34, 36 / 26; hand-over in the third step 163 / 269, 41 / 46, 32 / 31, 35 / 25.
-constexpr int64_t kCmQuadRows = 1000;
+// (With the statistics, in place, 1023 rows 47 / 52, 1535 44 / 43.)
+constexpr int64_t kCmQuadRows = 1000, kCmQuadStatRows = 1500;
 
 void finish_geometry(DevMat& d, int cn_rows, int up_rows, bool zen = false) {
   set_geometry(d, cn_rows, up_rows);
@@ -461,7 +462,7 @@ void finish_geometry(DevMat& d, int cn_rows, int up_rows, bool zen = false) {
     d.cm_snch = d.n > 0 ? static_cast<int32_t>(ceil_div(d.n, int64_t(zf::kCmSelChunk))) : 0;
     d.cm_unch = d.n > 0 ? static_cast<int32_t>(ceil_div(d.n, zf::kCmUnpackChunk)) : 0;
     d.vec = cm_vec_ok(d) ? 1 : 0;
-    d.cm_quads = d.n >= kCmQuadRows ? 1 : 0;
+    d.cm_quads = d.n >= kCmQuadStatRows ? 2 : d.n >= kCmQuadRows ? 1 : 0;
     const auto al16 = [](const void* p, int64_t ld) {
       return p != nullptr && aligned(p, 16) && ld % 8 == 0;
     };

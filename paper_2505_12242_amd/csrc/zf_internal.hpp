@@ -117,7 +117,8 @@ struct DevMat {
   int32_t cm_unch;   // channel-major: row chunks per channel (unpack)
   int32_t cm_qpt;    // channel-major: quads (4 elements) per thread in the update (kCmQpt / 2 or kCmQpt)
   int32_t cm_snch;   // channel-major: row chunks per channel of the selected-only Adam grid
-  int32_t cm_quads;  // channel-major, off the vector path: quads of any alignment (else elements)
+  int32_t cm_quads;  // channel-major, off the vector path: element by element (0), or quads of any
+                     // alignment, but for the packing update with the statistics (1), or there too (2)
   int32_t scat_vec;  // channel-major: 16-byte path of the weight scatter
   int32_t rv;        // row-major: the 16-byte update kernel is used (else per-column)
   int32_t rv_w;      // row-major 16-byte update: tile width (columns)

@@ -472,14 +472,15 @@ __device__ __forceinline__ void cm_pack_piece(int qpt, const Row16& rG, rsrc_t r
 // fn(path, e0, len) over the pieces of rows [e0, e0 + len): the whole of them on
 // the vector path; RAG kernels, off it: the whole quads (of matrices that take
 // them: cm_quads), then the rest.
-template <bool RAG, typename Fn>
+// STATS: an update with the statistics.
+template <bool RAG, bool STATS = false, typename Fn>
 __device__ __forceinline__ void cm_pieces(const DevMat& d, int64_t e0, int64_t len, Fn fn) {
   if constexpr (!RAG) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
   } else if (d.vec) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
   } else {
-    const int64_t n4 = d.cm_quads ? len & ~int64_t(3) : 0;
+    const int64_t n4 = d.cm_quads > (STATS ? 1 : 0) ? len & ~int64_t(3) : 0;
     if (n4 > 0) fn(std::integral_constant<int, kPathRag>{}, e0, n4);
     if (len > n4) fn(std::integral_constant<int, kPathElem>{}, e0 + n4, len - n4);
   }
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
   double ss = 0.0;
 
   if (!sel) {
-    cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG, STATS && !DEFP>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       if (mode == kRemap && d.st_P != nullptr) cm_swap_out<P>(d, j, w, e0, len);
@@ -747,7 +748,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
       }
     });
   } else if constexpr (ADAM) {
-    cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG, STATS && !DEFP>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
@@ -971,6 +972,9 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
   const int32_t kept = DEFP ? min(max(length - 1, 0), h.n) : 0;
   // each block walks one contiguous run of units, the runs in the
   // XCD-aware block order
+  // (ragged with deferred packing: single chunks -- pairs take 86 registers
+  // instead of 50 and their short channels 129 us instead of 96)
+  constexpr bool kPair = !(DEFP && RAG);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x, units);
   const int64_t per = (units + gridDim.x - 1) / gridDim.x;
   const int64_t u0 = b * per;
@@ -989,10 +993,11 @@ __global__ __launch_bounds__(kThreads) void cm_unpack_zen_kernel(const DevMat* _
     const int64_t local = u - off[lo];
     const int64_t j = local / d.cm_unch;
     const int64_t e0 = (local % d.cm_unch) * kCmUnpackChunk;
-    const bool pair = u + 1 < u1 && (local + 1) / d.cm_unch == j;
+    const bool pair = kPair && u + 1 < u1 && (local + 1) / d.cm_unch == j;
     const int64_t len = min(static_cast<int64_t>(pair ? 2 : 1) * kCmUnpackChunk, d.n - e0);
     if (pair) {
-      if constexpr (DEFP) cm_handover_rows_deferred<2 * kCmUnpackQpt, RAG, BATCH>(d, lo, j, e0, len, scale, h, kept);
+      if constexpr (DEFP && !RAG) cm_handover_rows_deferred<2 * kCmUnpackQpt, RAG, BATCH>(d, lo, j, e0, len, scale, h, kept);
+      else if constexpr (DEFP) {}  // (no pairs)
       else if (from_stage) cm_unpack_rows<true, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       else cm_unpack_rows<false, 2 * kCmUnpackQpt, RAG>(d, j, e0, len, scale);
       u += 2;
