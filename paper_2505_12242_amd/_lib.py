@@ -180,16 +180,14 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else (t.data_ptr() or None)
 
 
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-
-
 def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream.cuda_stream
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    # torch.cuda.current_stream().cuda_stream without the Stream object
-    return _raw_stream(_device())
+    # torch.cuda.current_stream().cuda_stream without the Stream object (looked
+    # up here: a torch without a GPU backend has neither name)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _mat(t: torch.Tensor, dtype, name: str, rows: Optional[int] = None,

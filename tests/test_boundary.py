@@ -5,6 +5,8 @@ import ctypes
 import math
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -42,6 +44,17 @@ def test_every_declared_function_is_exported_and_bound():
     for name in names:
         assert hasattr(raw, name), name
         assert name in bound, name
+
+
+def test_import_without_a_gpu_backend_in_torch():
+    """The package (its host functions) loads with a torch built without one."""
+    code = ("import torch\n"
+            "for name in [x for x in dir(torch._C) if x.startswith('_cuda_')]:\n"
+            "    delattr(torch._C, name)\n"
+            "import paper_2505_12242_amd as zf\n"
+            "assert zf.k_from_ratio(0.1, 4096) == 410\n")
+    run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr
 
 
 def test_status_strings():
