@@ -201,6 +201,17 @@ int pick_zen_rows(const std::vector<std::pair<int64_t, int64_t>>& shapes) {
   }
 }
 
+// Waves a block of the row-major column sums' second stage (blocks of kFinCols
+// columns): one where a column's partials are at most one round of loads for it
+// (1000000 columns of 2 partials, the scores with one / eight waves 49 / 53
+// us), and on grids whose blocks of eight would pass the 2^32 - 1 work-items of
+// a launch.
+int fin_segs(int32_t max_rb, int64_t blocks) {
+  const bool one = max_rb <= zf::kFinBatch ||
+                   blocks > ((int64_t(1) << 32) - 1) / (zf::kFinCols * zf::kFinSegs);
+  return one ? 1 : zf::kFinSegs;
+}
+
 void set_geometry(DevMat& d, int cn_rows, int up_rows) {
   d.cn_rpb = cn_rows;
   d.cn_cb = static_cast<int32_t>(ceil_div(d.m, zf::kColnormCols));
@@ -700,7 +711,8 @@ zf_status zf_colnorm(const uint16_t* grad, int64_t n, int64_t m, int64_t ld_grad
     e = zf::launch_cm_colnorm(single_table(d), d, colnorm_grid(d), as_stream(stream));
   else
     e = zf::launch_colnorm(single_table(d), d, colnorm_grid(d), single_table(d),
-                           ceil_div(m, zf::kFinCols), static_cast<double*>(ws),
+                           ceil_div(m, zf::kFinCols),
+                           fin_segs(d.cn_rb, ceil_div(m, zf::kFinCols)), static_cast<double*>(ws),
                            as_stream(stream));
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -930,6 +942,7 @@ struct zf_plan {
   int64_t blk_cn = 0, blk_fin = 0, blk_top = 0, blk_up = 0, blk_unp = 0, blk_zen = 0, blk_zp = 0,
           blk_upv = 0, blk_sel = 0;
   int64_t k_total = 0, u_total = 0;
+  int32_t max_cn_rb = 0, max_zn_rb = 0;  // row-major: the most partials of a column
   RmSet set;  // row-major: what the choice of the update kernel looks at
   bool ragged = false;  // channel-major: some matrix is off the aligned vector path
   bool can_colnorm = true, can_topk = true, can_adam = true, can_remap = true, can_pack = true,
@@ -1122,6 +1135,8 @@ zf_status build_plan_impl(const zf_matrix* mats, int32_t nmats, zf_plan* p) {
     p->k_total += d.k;
     p->u_total += d.m - d.k;
     p->set.add(d);
+    p->max_cn_rb = std::max(p->max_cn_rb, d.cn_rb);
+    p->max_zn_rb = std::max(p->max_zn_rb, d.zn_rb);
     p->ragged = p->ragged || is_ragged(d);
     off_cn[q] = p->blk_cn;
     off_fin[q] = p->blk_fin;
@@ -1258,7 +1273,8 @@ zf_status zf_plan_colnorm(zf_plan* p, zf_stream stream) {
     e = zf::launch_cm_colnorm(t, p->mats[0], p->blk_cn, as_stream(stream));
   } else {
     const Table tf{p->d_mats, p->d_off_fin, p->nmats, p->ragged};
-    e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin, p->d_ws, as_stream(stream));
+    e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin,
+                           fin_segs(p->max_cn_rb, p->blk_fin), p->d_ws, as_stream(stream));
   }
   return e == hipSuccess ? ZF_OK : hip_fail(e);
 }
@@ -1271,7 +1287,8 @@ zf_status zf_plan_colnorm_stage(zf_plan* p, zf_stream stream) {
     e = zf::launch_cm_colnorm(t, p->mats[0], p->blk_cn, as_stream(stream), 1);
   } else {
     const Table tf{p->d_mats, p->d_off_fin, p->nmats, p->ragged};
-    e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin, p->d_ws, as_stream(stream),
+    e = zf::launch_colnorm(t, p->mats[0], p->blk_cn, tf, p->blk_fin,
+                           fin_segs(p->max_cn_rb, p->blk_fin), p->d_ws, as_stream(stream),
                            true);
   }
   return e == hipSuccess ? ZF_OK : hip_fail(e);
@@ -1568,7 +1585,8 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
                              s, p->d_ws, zst);
     if (e != hipSuccess) return hip_fail(e);
     const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
-    e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
+    e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, fin_segs(p->max_zn_rb, p->blk_zen), p->mats[0],
+                          p->d_ws, p->d_zb, s);
   } else if (vec) {
     // A refresh on 16-byte buffers: Adam alone in the per-column kernel (first:
     // it reads what the caller gives as state sources, the packing writes),
@@ -1584,7 +1602,8 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
                              p->d_ws);
     if (e != hipSuccess) return hip_fail(e);
     const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
-    e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
+    e = zf::launch_rm_zen(tp, 0, tz, p->blk_zen, fin_segs(p->max_zn_rb, p->blk_zen), p->mats[0],
+                          p->d_ws, p->d_zb, s);
   } else {
     // the per-column update (with zst the kernel derives the phase: 1 on a
     // refresh or after an ended interval, else the interval's length + 1)
@@ -1592,7 +1611,8 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
                           pd, zst);
     if (e != hipSuccess) return hip_fail(e);
     const Table tp{p->d_mats, p->d_off_zp, p->nmats, p->ragged};
-    e = zf::launch_rm_zen(tp, p->blk_zp, tz, p->blk_zen, p->mats[0], p->d_ws, p->d_zb, s);
+    e = zf::launch_rm_zen(tp, p->blk_zp, tz, p->blk_zen, fin_segs(p->max_zn_rb, p->blk_zen), p->mats[0],
+                          p->d_ws, p->d_zb, s);
   }
   if (e != hipSuccess) return hip_fail(e);
   e = zf::launch_zen_total(p->d_zb, p->blk_zen, p->k_total, p->u_total, tau,

@@ -240,15 +240,16 @@ __device__ __forceinline__ void buf_put_b64(u32x2 v, rsrc_t r, uint32_t voff, ui
 
 // Second stage of the row-major column sums: column j's cn_rb row-block
 // partials (rows of m doubles at p) added in a fixed order -- wave w of the
-// block the w-th contiguous share of them, in row-block order, then the waves'
-// sums in wave order through `red`.  Every thread of the block calls it; the
-// result is valid in the first kFinCols threads.
+// block's SEGS the w-th contiguous share of them, in row-block order, then the
+// waves' sums in wave order through `red`.  Every thread of the block calls it;
+// the result is valid in the first kFinCols threads.
+template <int SEGS>
 __device__ __forceinline__ double finalize_sum(const double* __restrict__ p, int32_t rb, int64_t m,
-                                               int64_t j, double (&red)[kFinSegs][kFinCols]) {
-  constexpr int kBatch = 8;  // loads in flight per lane
+                                               int64_t j, double (&red)[SEGS][kFinCols]) {
+  constexpr int kBatch = kFinBatch;  // loads in flight per lane
   const int lane = threadIdx.x & 63;
   const int wave = uniform_i32(threadIdx.x >> 6);
-  const int32_t per = (rb + kFinSegs - 1) / kFinSegs;
+  const int32_t per = (rb + SEGS - 1) / SEGS;
   const int32_t r1 = min(rb, (wave + 1) * per);
   double s = 0.0;
   if (j < m) {
@@ -261,11 +262,12 @@ __device__ __forceinline__ double finalize_sum(const double* __restrict__ p, int
       for (int b = 0; b < kBatch; ++b) s += v[b];
     }
   }
+  if constexpr (SEGS == 1) return s;
   red[wave][lane] = s;
   __syncthreads();
   s = red[0][lane];
 #pragma unroll
-  for (int w = 1; w < kFinSegs; ++w) s += red[w][lane];
+  for (int w = 1; w < SEGS; ++w) s += red[w][lane];
   return s;
 }
 

@@ -17,8 +17,8 @@ constexpr int kThreads = 256;
 constexpr int kColnormCols = 512;
 constexpr int kUpdateCols = 256;
 constexpr int kFinCols = 64;  // row-major column sums, second stage: columns per block
-constexpr int kFinSegs = 8;   // and waves, each adding a share of their partials
-constexpr int kFinThreads = kFinCols * kFinSegs;
+constexpr int kFinSegs = 8;   // and waves, each adding a share of their partials (or one: fin_segs)
+constexpr int kFinBatch = 8;  // partials a lane has in flight
 constexpr int kTopkThreads = 1024;
 
 // Row-major update with 16-byte accesses: a block covers rv_w <= kRvMaxCols
@@ -176,8 +176,9 @@ AdamK adam_consts(const zf_adam_hparams& hp, int64_t step);
 // Kernel launchers (zf_kernels.hip).  `blocks` is the grid size.
 // stage: also copy every element read to the same place of acc1 (the
 // bf16 first-step stage; row-major plans that have one).
+// segs: waves a block of the second stage (1 or kFinSegs).
 hipError_t launch_colnorm(const Table& t, const DevMat& one, int64_t blocks,
-                          const Table& tf, int64_t fin_blocks, double* ws, hipStream_t s,
+                          const Table& tf, int64_t fin_blocks, int segs, double* ws, hipStream_t s,
                           bool stage = false);
 hipError_t launch_topk(const Table& t, const DevMat& one, int64_t blocks, hipStream_t s);
 // pend != nullptr: fused Adam + pack in kRemap against the store, with the
@@ -294,8 +295,8 @@ hipError_t launch_zen_finalize(const Table& t, const DevMat& one, int64_t blocks
 // per-column partials over the column-score row blocks into zs (the plan's
 // column-score workspace), then the row-major finalize into zb.
 hipError_t launch_rm_zen(const Table& tp, int64_t partial_blocks, const Table& tf,
-                         int64_t finalize_blocks, const DevMat& one, double* zs, double* zb,
-                         hipStream_t s);
+                         int64_t finalize_blocks, int segs, const DevMat& one, double* zs,
+                         double* zb, hipStream_t s);
 // One block: sums zb in a fixed order and evaluates the trigger.
 // Streaming reference passes (zf_measure.h): kind 0 read, 1 copy, 2
 // read-modify-write in place.

@@ -123,15 +123,16 @@ __global__ __launch_bounds__(kThreads) void colnorm_partial_kernel(const DevMat*
 // column, 16 blocks on the chip), seven times the pass over G itself.  Here
 // the kFinSegs waves of a block take a contiguous share of the partials of 64
 // columns each, 8 loads in flight (finalize_sum): 4.3 us, and 5.8 us against 27.9 us for the layer of
-// seven Llama-2-7B weights (16 to 43 partials a column).
-template <bool BATCHED>
-__global__ __launch_bounds__(kFinThreads) void colnorm_finalize_kernel(
+// seven Llama-2-7B weights (16 to 43 partials a column).  Few partials are one
+// round of loads for a single wave (SEGS 1).
+template <bool BATCHED, int SEGS>
+__global__ __launch_bounds__(kFinCols * SEGS) void colnorm_finalize_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one, const double* __restrict__ ws) {
   int64_t local;
   const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
   const int64_t j = local * kFinCols + (threadIdx.x & 63);
-  __shared__ double red[kFinSegs][kFinCols];
-  const double s = finalize_sum(ws + d.cn_ws, d.cn_rb, d.m, j, red);
+  __shared__ double red[SEGS][kFinCols];
+  const double s = finalize_sum<SEGS>(ws + d.cn_ws, d.cn_rb, d.m, j, red);
   if (threadIdx.x < kFinCols && j < d.m) d.norms[j] = static_cast<float>(s);
 }
 
@@ -876,8 +877,20 @@ __global__ __launch_bounds__(kThreads) void rm_handover_deferred_kernel(
                          (T).nmats, __VA_ARGS__);                                          \
   } while (0)
 
+template <int SEGS>
+static void launch_fin(const Table& t, const DevMat& one, int64_t blocks, const double* ws,
+                       hipStream_t s) {
+  const dim3 grid(static_cast<uint32_t>(blocks)), block(kFinCols * SEGS);
+  if (t.mats != nullptr)
+    hipLaunchKernelGGL((colnorm_finalize_kernel<true, SEGS>), grid, block, 0, s, t.mats, t.off,
+                       t.nmats, one, ws);
+  else
+    hipLaunchKernelGGL((colnorm_finalize_kernel<false, SEGS>), grid, block, 0, s, t.mats, t.off,
+                       t.nmats, one, ws);
+}
+
 hipError_t launch_colnorm(const Table& t, const DevMat& one, int64_t blocks, const Table& tf,
-                          int64_t fin_blocks, double* ws, hipStream_t s, bool stage) {
+                          int64_t fin_blocks, int segs, double* ws, hipStream_t s, bool stage) {
   (void)hipGetLastError();
   if (blocks > 0) {
     const dim3 grid(static_cast<uint32_t>(blocks));
@@ -897,9 +910,10 @@ hipError_t launch_colnorm(const Table& t, const DevMat& one, int64_t blocks, con
                            t.mats, t.off, t.nmats, one, ws);
     }
   }
-  if (fin_blocks > 0)
-    ZF_LAUNCH(colnorm_finalize_kernel, dim3(static_cast<uint32_t>(fin_blocks)),
-              dim3(kFinThreads), s, tf, one, static_cast<const double*>(ws));
+  if (fin_blocks > 0 && segs == 1)
+    launch_fin<1>(tf, one, fin_blocks, ws, s);
+  else if (fin_blocks > 0)
+    launch_fin<kFinSegs>(tf, one, fin_blocks, ws, s);
   return hipGetLastError();
 }
 

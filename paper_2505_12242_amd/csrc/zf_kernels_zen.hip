@@ -111,16 +111,16 @@ __global__ __launch_bounds__(kZenCols) void rm_zen_partial_kernel(const DevMat* 
 // The partials are added as in the column scores' second stage; the block's
 // 64 square roots then in a fixed butterfly (8.4 us for the seven weights of a
 // Llama-2-7B layer, 39.0 us with one thread per column: latency, see there).
-template <bool BATCHED>
-__global__ __launch_bounds__(kFinThreads) void rm_zen_finalize_kernel(
+template <bool BATCHED, int SEGS>
+__global__ __launch_bounds__(kFinCols * SEGS) void rm_zen_finalize_kernel(
     const DevMat* __restrict__ mats, const int64_t* __restrict__ off, int32_t nmats, DevMat one,
     const double* __restrict__ zs, double* __restrict__ zb) {
   int64_t local;
   const DevMat& d = get_mat<BATCHED>(mats, off, nmats, one, local);
   const int64_t b = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t c = local * kFinCols + (threadIdx.x & 63);
-  __shared__ double red[kFinSegs][kFinCols];
-  const double s = finalize_sum(zs + d.cn_ws, d.zn_rb, d.m, c, red);
+  __shared__ double red[SEGS][kFinCols];
+  const double s = finalize_sum<SEGS>(zs + d.cn_ws, d.zn_rb, d.m, c, red);
   if (threadIdx.x >= kFinCols) return;
   double root_sel = 0.0, root_acc = 0.0;
   if (c < d.m) {
@@ -211,16 +211,19 @@ hipError_t launch_zen_finalize(const Table& t, const DevMat& one, int64_t blocks
 }
 
 hipError_t launch_rm_zen(const Table& tp, int64_t partial_blocks, const Table& tf,
-                         int64_t finalize_blocks, const DevMat& one, double* zs, double* zb,
-                         hipStream_t s) {
+                         int64_t finalize_blocks, int segs, const DevMat& one, double* zs,
+                         double* zb, hipStream_t s) {
   (void)hipGetLastError();
   if (partial_blocks > 0)
     hipLaunchKernelGGL((rm_zen_partial_kernel<true>), dim3(static_cast<uint32_t>(partial_blocks)),
                        dim3(kZenCols), 0, s, tp.mats, tp.off, tp.nmats, one, zs);
-  if (finalize_blocks > 0)
-    hipLaunchKernelGGL((rm_zen_finalize_kernel<true>),
-                       dim3(static_cast<uint32_t>(finalize_blocks)), dim3(kFinThreads), 0, s, tf.mats,
+  const dim3 grid(static_cast<uint32_t>(finalize_blocks));
+  if (finalize_blocks > 0 && segs == 1)
+    hipLaunchKernelGGL((rm_zen_finalize_kernel<true, 1>), grid, dim3(kFinCols), 0, s, tf.mats,
                        tf.off, tf.nmats, one, zs, zb);
+  else if (finalize_blocks > 0)
+    hipLaunchKernelGGL((rm_zen_finalize_kernel<true, kFinSegs>), grid, dim3(kFinCols * kFinSegs), 0,
+                       s, tf.mats, tf.off, tf.nmats, one, zs, zb);
   return hipGetLastError();
 }
 

@@ -35,6 +35,14 @@ def test_row_major_scores_second_stage(n, m):
     assert ok, (n, m, worst)
 
 
+# ... and so many columns that blocks of eight waves would pass the work-items
+# of one launch (one partial a column: exact squares, rounded once).
+def test_row_major_scores_of_a_very_wide_row():
+    m = (1 << 29) + 5
+    g = torch.randn(1, m, device="cuda", dtype=torch.bfloat16)
+    assert torch.equal(zf.colnorm(g), (g[0].float() ** 2))
+
+
 # Selection: columns at the edges of the register variants (1, 4, 8, 16 and 32
 # words of 64 columns for each of 16 waves) and beyond the last; scores that
 # spread, that share one radix digit, and that tie.

@@ -164,6 +164,15 @@ def scenarios(r):
             out[f"kept {n} {steps}"] = [
                 r.deferred(p, [p] * (steps - 1)),
                 r.call("zf_plan_handover_zen_deferred", p, hs, steps - 1, r.state, None)]
+    # second stage of the row-major column sums
+    for n, m in ((128, 4096), (144, 4096), (4096, 4096), (1, (1 << 30) - 1), (0, 64)):
+        ws = r.L.LIB.zf_colnorm_workspace_bytes(n, m, RM)
+        out[f"scores {n} {m}"] = [r.call("zf_colnorm", r.addr(2 * n * m, 0), n, m, m, RM,
+                                         r.addr(4 * m, 0), r.addr(ws, 0), ws, None)]
+    for name, shapes in (("few", [(128, 72)] * 3), ("many", [(144, 72), (4096, 72)]),
+                         ("huge", [(4096, 72)] + [(1, (1 << 26) - 8)] * 9)):
+        p = r.plan([r.matrix(n, m, RM, zen=True) for n, m in shapes])
+        out["scores " + name] = [r.call("zf_plan_colnorm", p, None), r.zen(p)]
     return out
 
 
@@ -285,3 +294,16 @@ def test_channel_major_gradients_in_flight(routes, n, steps):
         f"cm_handover_deferred_kernel<{rag}, {8 if n > 2048 else 4}>"]
     assert [x[0] for x in gated] == [
         f"cm_unpack_zen_kernel<true, {rag}, {8 if n > 2048 and steps > 4 else 4}>"]
+
+
+@pytest.mark.parametrize("name,waves", [("128 4096", 1), ("144 4096", 8), ("4096 4096", 8),
+                                        (f"1 {(1 << 30) - 1}", 1), ("0 64", 1), ("few", 1),
+                                        ("many", 8), ("huge", 1)])
+def test_row_major_sums_second_stage(routes, name, waves):
+    """One wave a block up to eight partials a column, and where eight would not
+    fit one launch, whose work-items are a 32-bit count."""
+    calls = routes["scores " + name]
+    for status, launches in calls:
+        assert status == 0
+        assert all(grid * block < 1 << 32 for _, grid, block in launches)
+        assert [block for k, _, block in launches if "finalize" in k] == [64 * waves]
