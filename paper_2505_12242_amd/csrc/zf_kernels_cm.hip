@@ -1053,19 +1053,20 @@ template <bool ADAM, bool PACK, bool STATS, bool HAND, bool PEND, bool SELG, int
 static void launch_cm_update_r(const Table& t, const DevMat& one, dim3 grid, const AdamK& c,
                                int32_t mode, int32_t first, double* zs, float scale,
                                hipStream_t s, const Pending& pd, const ZenState* zst) {
+  // a single matrix comes without the statistics, the owed update, a stage (so
+  // no second step of its own) and rows to zero: see launch_cm_update
+  constexpr bool kSingle = !STATS && !PEND && PH != 2 && !(SELG && HAND);
   if (t.mats != nullptr)
     hipLaunchKernelGGL((cm_update_kernel<true, ADAM, PACK, STATS, HAND, PEND, SELG, PH, false, RAG>),
                        grid, dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode,
                        first, zs, scale, pd, zst, HistTable{});
-  else
+  else if constexpr (kSingle)
     hipLaunchKernelGGL(
         (cm_update_kernel<false, ADAM, PACK, STATS, HAND, PEND, SELG, PH, false, RAG>), grid,
         dim3(kThreads), kCmUpdateLds, s, t.mats, t.off, t.nmats, one, c, mode, first, zs, scale,
         pd, zst, HistTable{});
 }
 
-// The interval's phase is a compile-time constant in the aligned launches of
-// the fixed schedule; the ragged kernels, larger already, take it at run time.
 template <bool ADAM, bool PACK, bool STATS, bool HAND, bool PEND = false, bool SELG = false,
           int PH = 0>
 static void launch_cm_update_t(const Table& t, const DevMat& one, dim3 grid, const AdamK& c,
@@ -1073,8 +1074,8 @@ static void launch_cm_update_t(const Table& t, const DevMat& one, dim3 grid, con
                                hipStream_t s, const Pending& pd = Pending{},
                                const ZenState* zst = nullptr) {
   if (t.ragged)
-    launch_cm_update_r<ADAM, PACK, STATS, HAND, PEND, SELG, 0, true>(t, one, grid, c, mode, first,
-                                                                     zs, scale, s, pd, zst);
+    launch_cm_update_r<ADAM, PACK, STATS, HAND, PEND, SELG, PH, true>(t, one, grid, c, mode, first,
+                                                                      zs, scale, s, pd, zst);
   else
     launch_cm_update_r<ADAM, PACK, STATS, HAND, PEND, SELG, PH, false>(t, one, grid, c, mode,
                                                                        first, zs, scale, s, pd, zst);
@@ -1101,6 +1102,7 @@ hipError_t launch_cm_adam_selected_grid(const Table& t, const DevMat& one, int64
                                         bool zero_out) {
   (void)hipGetLastError();
   if (blocks <= 0) return hipSuccess;
+  if (zero_out && t.mats == nullptr) return hipErrorInvalidValue;
   const dim3 grid(static_cast<uint32_t>(blocks));
   if (zero_out)
     launch_cm_update_t<true, false, false, true, false, true>(t, one, grid, c, mode, 0, nullptr,
@@ -1119,6 +1121,8 @@ hipError_t launch_cm_update(const Table& t, const DevMat& one, int64_t blocks, c
   if (blocks <= 0) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(blocks));
   if ((zs != nullptr || handover) && !(adam && pack)) return hipErrorInvalidValue;
+  if (t.mats == nullptr && (zs != nullptr || pend != nullptr || first == 2))
+    return hipErrorInvalidValue;  // plans only
   if (zs != nullptr && handover && zst == nullptr) return hipErrorInvalidValue;
   if (zst != nullptr && (zs == nullptr || pend != nullptr)) return hipErrorInvalidValue;
   if (pend != nullptr) {

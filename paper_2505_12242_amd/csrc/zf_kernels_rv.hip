@@ -5,8 +5,9 @@
 // A lane that owns one column and walks the rows moves 2- and 4-byte
 // elements; on this chip such per-lane narrow accesses stream at about two
 // thirds of the rate of 16-byte ones.  Here a block owns a tile of up to
-// kRvMaxCols columns (equal-width tiles per matrix, multiples of 8) and
-// rv_rows rows, and works in two index spaces:
+// kRvMaxCols columns (equal-width tiles per matrix, multiples of 64 where that
+// needs no more tiles, else of 8) and rv_rows rows, and works in two index
+// spaces:
 //   column space: G is loaded with one 16-byte load per lane (8 columns,
 //     two rows per block-wide load) and staged in LDS; the fused
 //     hand-over's output rows are assembled in LDS and stored with 16-byte
@@ -28,9 +29,9 @@
 //     every tile width, slot alignment and selected count).
 // Rows are staged kRvBatch at a time, every load of a batch issued before
 // the first wait.  The Adam part serves steps with the compact states in place;
-// on a refresh step, whose entering and leaving columns read and write their
-// sources element by element, the per-column kernel runs Adam alone and this
-// one the packing (and the statistics, and the hand-over).
+// a refresh step, whose entering and leaving columns read and write their
+// sources element by element, is the per-column kernel's, but under Zen-auto,
+// where that one runs Adam alone and this one the packing with the statistics.
 //
 // The bf16 first-step stage (acc1, optional; one bf16 row per gradient row):
 // on an interval's first step (first == 1) the block stores the G rows it
@@ -41,8 +42,11 @@
 //
 // PH: the interval's phase as a compile-time constant (1: its first step, 2: its
 // second, where the stage may be read), or 0 to take it from `first` (later
-// steps, and Zen-auto, which has no stage): each phase holds only the registers
-// and the LDS it needs.
+// steps, and Zen-auto, which has no stage).  Only the second step then holds the
+// LDS rows and the registers of the stage: fused update of a plan, first / second
+// / later step 84 / 95 / 81 registers a lane, with the hand-over 89 / 109 / 91
+// (the 64-bit addresses of the gradient loads, which take rows of any alignment,
+// among them).
 //
 // STATS (Zen-auto; with HAND on an end the caller
 // forces, the sums before the scale): each lane also sums, in fp64 and
@@ -126,6 +130,7 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
                                                              HistTable hist,
                                                              const ZenState* __restrict__ zst) {
   static_assert(!STATS || PACK, "statistics of the packing pass");
+  static_assert(!HAND || (ADAM && PACK), "the hand-over of the fused update");
   static_assert(!DEF || (BATCHED && !ADAM && !PACK && !HAND && !STATS && PH == 0),
                 "the deferred hand-over pass");
   // Zen-auto with the interval driven on the device (steps in place):
@@ -173,8 +178,8 @@ __global__ __launch_bounds__(kThreads) void rv_update_kernel(const DevMat* __res
   const bool is_q = tid < nqf;
   const bool is_e = !is_q && tid < nqf + ne;
   // (without ADAM the selected slots' lanes take the statistics of their
-  // gradient and zero the hand-over at their columns)
-  const bool is_s = (ADAM || STATS || HAND) && tid >= nqf + ne && cs > 0;
+  // gradient)
+  const bool is_s = (ADAM || STATS) && tid >= nqf + ne && cs > 0;
 
   // The lane's elements: slot s[e] (byte offset vs[e] in its buffer's
   // row), column offset cj[e] in the tile, valid bit e.
@@ -534,11 +539,14 @@ template <bool ADAM, bool PACK, bool HAND, bool STATS, int PH>
 void launch_rv_a(const Table& t, const DevMat& one, dim3 grid, const AdamK& c, int32_t first,
                  float scale, hipStream_t s, double* zs, const ZenState* zst = nullptr) {
   const HistTable none{};
+  // a single matrix comes without the statistics and without a stage (so no
+  // second step of its own): see launch_rv_update
+  constexpr bool kSingle = !STATS && PH != 2;
   if (t.mats != nullptr)
     hipLaunchKernelGGL((rv_update_kernel<true, ADAM, PACK, HAND, STATS, PH, false>), grid,
                        dim3(kThreads), 0, s, t.mats, t.off, t.nmats, one, c, first, scale, zs,
                        none, zst);
-  else
+  else if constexpr (kSingle)
     hipLaunchKernelGGL((rv_update_kernel<false, ADAM, PACK, HAND, STATS, PH, false>), grid,
                        dim3(kThreads), 0, s, t.mats, t.off, t.nmats, one, c, first, scale, zs,
                        none, zst);
@@ -568,16 +576,17 @@ hipError_t launch_rv_update(const Table& t, const DevMat& one, int64_t blocks, c
   (void)hipGetLastError();
   if (blocks <= 0) return hipSuccess;
   const dim3 grid(static_cast<uint32_t>(blocks));
-  if ((handover || zs != nullptr) && !pack) return hipErrorInvalidValue;
+  if (handover && !(adam && pack)) return hipErrorInvalidValue;
+  if (zs != nullptr && !pack) return hipErrorInvalidValue;
+  if (t.mats == nullptr && (zs != nullptr || first == 2)) return hipErrorInvalidValue;  // plans only
   if (adam && mode != kInplace) return hipErrorInvalidValue;  // refresh: per-column kernel
   if (zst != nullptr && (zs == nullptr || !adam)) return hipErrorInvalidValue;  // Zen-auto steps only
   if (zs != nullptr) {
-    if (handover && (zst == nullptr || !adam)) return hipErrorInvalidValue;
+    if (handover && zst == nullptr) return hipErrorInvalidValue;
     if (handover) launch_rv_t<true, true, true, true>(t, one, grid, c, first, 1.0f, s, zs, zst);
     else if (adam) launch_rv_t<true, true, false, true>(t, one, grid, c, first, 1.0f, s, zs, zst);
     else launch_rv_t<false, true, false, true>(t, one, grid, c, first, 1.0f, s, zs);
-  } else if (handover && adam) launch_rv_t<true, true, true>(t, one, grid, c, first, scale, s);
-  else if (handover) launch_rv_t<false, true, true>(t, one, grid, c, first, scale, s);
+  } else if (handover) launch_rv_t<true, true, true>(t, one, grid, c, first, scale, s);
   else if (adam && pack) launch_rv_t<true, true, false>(t, one, grid, c, first, 1.0f, s);
   else if (adam) launch_rv_t<true, false, false>(t, one, grid, c, first, 1.0f, s);
   else if (pack) launch_rv_t<false, true, false>(t, one, grid, c, first, 1.0f, s);
