@@ -1624,8 +1624,8 @@ zf_status plan_update_zen(zf_plan* p, const AdamK& c, int32_t mode, int32_t firs
 bool zen_args_ok(const zf_plan* p, const zf_adam_hparams* hp, int64_t step, double tau,
                  const zf_zen_totals* totals) {
   static_assert(sizeof(zf_zen_totals) == sizeof(zf::ZenTotals), "zen totals layout");
-  // (row-major Zen-auto statistics of refresh steps read the packed buffer
-  // in a separate pass: no stage there)
+  // (the row-major statistics are those of the packed buffer, which a separate
+  // pass may read: no stage there)
   return p != nullptr && p->can_zen && p->can_adam && p->can_pack && hparams_ok(hp) &&
          !(p->has_acc1 && p->layout == zf::kRowMajor) &&
          step >= 1 && tau >= 0.0 && totals != nullptr && aligned(totals, 8);

@@ -50,8 +50,10 @@ inline void host_adam_elem(float g, float& p, float& m, float& v, const zf::Adam
 }
 
 // A contiguous run of `len` elements: gradient a * scale, states p/m/v,
-// bf16 output w.  Written as independent element loops so that the
-// compiler vectorises them (every vector lane is the same IEEE operation).
+// bf16 output w.  The elements are independent, but the loop is compiled as
+// scalar code: std::sqrt may set errno, which keeps the compiler from vector
+// instructions (3.9 ns an element on one thread; with -fno-math-errno it takes
+// four lanes and 1.8 ns, with the same bits).
 void host_adam_run(const float* __restrict__ a, float scale, float* __restrict__ p,
                    float* __restrict__ m, float* __restrict__ v, uint16_t* __restrict__ w,
                    int64_t len, const zf::AdamK& c) {

@@ -120,7 +120,7 @@ struct DevMat {
   int32_t cm_quads;  // channel-major, off the vector path: element by element (0), or quads of any
                      // alignment, but for the packing update with the statistics (1), or there too (2)
   int32_t scat_vec;  // channel-major: 16-byte path of the weight scatter
-  int32_t rv;        // row-major: the 16-byte update kernel is used (else per-column)
+  int32_t rv;        // row-major: the 16-byte update kernel can be used (its strides fit)
   int32_t rv_w;      // row-major 16-byte update: tile width (columns)
   int32_t rv_cb;     // row-major 16-byte update: column tiles
   int32_t rv_rows;   // row-major 16-byte update and Zen-auto statistics: rows per block

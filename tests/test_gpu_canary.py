@@ -187,9 +187,9 @@ def test_no_write_outside_deferred_handover(n, m, padded, layout):
     compact states, W and the hand-over, fills the hand-over, leaves the
     earlier gradients alone, and equals the oracle: Adam in place on the
     selected columns, the hand-over of pack_accumulate over the four
-    gradients times fp32(1/4).  Earlier gradients with 16-byte rows keep
-    the row-major 16-byte kernel; unpadded ones (ld = width) take the
-    per-column passes."""
+    gradients times fp32(1/4).  Row-major, this step's buffers have
+    16-byte rows, so the 16-byte hand-over runs, which reads earlier
+    gradients with 16-byte rows and unpadded ones (ld = width) alike."""
     ratio = 0.1
     k = zf.k_from_ratio(ratio, m)
     rng = np.random.default_rng(n * 1000 + m)

@@ -2,8 +2,9 @@
 steps with the compact states in place (and pack-only calls) when G rows are
 16-byte aligned (row stride a multiple of 8 bf16) and the packed buffer, the
 compact states and the hand-over rows are 16-byte aligned with row strides
-that are multiples of 4 floats; refresh steps and other buffers take the
-per-column kernel.  Parity with the oracle bit for bit (states, weights,
+that are multiples of 4 floats; refresh steps, and other buffers on sets of
+the sizes here, take the per-column kernel (test_host_routes.py holds the
+rule).  Parity with the oracle bit for bit (states, weights,
 packed buffer, hand-over) over
 
 * tile raggedness: widths below, at and above the 1000-column tile limit,

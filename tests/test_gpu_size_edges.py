@@ -73,13 +73,13 @@ def test_selection_variants(m, kind):
         assert np.array_equal(got.prefix.cpu().numpy(), want.prefix), (m, kind, ratio)
 
 
-# Row-major Zen-auto: the 16-byte update with its statistics, and on a refresh
-# the packing pass with them after the per-column Adam, on gradient rows that
-# are 16-byte aligned and that are not, against the channel-major kernels:
-# identical states, weights and sums, statistics up to the order of the fp64
-# sums (half an ulp of fp32 on either side).  Rows at the edges of the row
-# batches and row blocks, columns at the edges of the tiles (multiples of 64 up
-# to 960, else of 8 up to 1000).
+# Row-major Zen-auto on 16-byte rows (the 16-byte update with its statistics, on a
+# refresh the packing pass with them after the per-column Adam) and off them (at
+# these sizes the per-column update and a statistics pass), against the
+# channel-major kernels: identical states, weights and sums, statistics up to
+# the order of the fp64 sums (half an ulp of fp32 on either side).  Rows at the
+# edges of the row batches and row blocks, columns at the edges of the tiles
+# (multiples of 64 up to 960, else of 8 up to 1000).
 @pytest.mark.parametrize("n", [1, 15, 17, 129])
 @pytest.mark.parametrize("m", [8, 960, 961, 1000, 1921])
 def test_row_major_zen_against_channel_major(n, m):
@@ -119,15 +119,19 @@ def test_row_major_zen_against_channel_major(n, m):
             plan.update_zen(zf.AdamHparams(lr=1e-3), t + 1, mode, 1 + (t == 1), 4, 1.0, totals)
             torch.cuda.synchronize()
             bits = [bits_np(w)] + [f32_np(x) for x in (acc, *st[p])]
-            out.append(([x.T if cm else x for x in bits], [f32_np(x) for x in sq]))
+            out.append(([x.T if cm else x for x in bits], [f32_np(x) for x in sq],
+                        zf.ZenTotals.from_bytes(totals.cpu().numpy().tobytes())))
             plan.close()
         got.append(out)
     for form, other in zip(("aligned", "unaligned"), got[1:]):
-        for t, ((bits, stats), (bits2, stats2)) in enumerate(zip(got[0], other)):
+        for t, ((bits, stats, tot), (bits2, stats2, tot2)) in enumerate(zip(got[0], other)):
             for i, (a, b) in enumerate(zip(bits, bits2)):
                 assert same_bits(a, b), (form, n, m, t, i)
             for a, b in zip(stats, stats2):
                 assert rel_close(b, a, 2.0 ** -22)[0], (form, n, m, t)
+            # sums over columns of the roots of those: no column is off by more
+            assert rel_close([tot2.sum_sel, tot2.sum_acc], [tot.sum_sel, tot.sum_acc], 2.0 ** -22)[0]
+            assert (tot2.k_total, tot2.u_total) == (tot.k_total, tot.u_total)
 
 
 # Row-major sets that are wide and large enough for the 16-byte update although

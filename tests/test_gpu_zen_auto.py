@@ -406,7 +406,8 @@ def test_zen_deferred_rejects_bad_arguments():
 def test_rowmajor_fused_statistics_equal_separate_pass():
     """Row-major plans: the statistics fused into the 16-byte update (aligned,
     padded buffers) and the separate statistics pass (the same data in
-    unaligned buffers, per-column update) write the same partials: the
+    unaligned buffers, which on sets of this size take the per-column update:
+    test_host_routes.py) write the same partials: the
     per-channel statistics, the totals, the states and the packed buffer are
     equal bit for bit, over an init step and two in-place steps."""
     from tests._gpu import bf16_dev, bits_np

@@ -164,6 +164,8 @@ def scenarios(r):
             out[f"kept {n} {steps}"] = [
                 r.deferred(p, [p] * (steps - 1)),
                 r.call("zf_plan_handover_zen_deferred", p, hs, steps - 1, r.state, None)]
+    # column tiles of the row-major 16-byte update (one row: one row block)
+    out["tiles"] = {str(m): r.update(r.plan([r.matrix(1, m, RM)]), adam=0) for m in TILE_COLUMNS}
     # second stage of the row-major column sums
     for n, m in ((128, 4096), (144, 4096), (4096, 4096), (1, (1 << 30) - 1), (0, 64)):
         ws = r.L.LIB.zf_colnorm_workspace_bytes(n, m, RM)
@@ -175,6 +177,9 @@ def scenarios(r):
         out["scores " + name] = [r.call("zf_plan_colnorm", p, None), r.zen(p)]
     return out
 
+
+TILE_COLUMNS = [1, 8, 63, 64, 65, 960, 961, 1000, 1001, 1024, 1920, 1921, 2000, 2001, 4096, 5120,
+                8192, 11008, 13824, 28672, 32000, 70001]
 
 # name, shapes, and how their buffers lie (off16 / off32: bytes past a 16-byte
 # boundary, rows then unpadded)
@@ -307,3 +312,12 @@ def test_row_major_sums_second_stage(routes, name, waves):
         assert status == 0
         assert all(grid * block < 1 << 32 for _, grid, block in launches)
         assert [block for k, _, block in launches if "finalize" in k] == [64 * waves]
+
+
+@pytest.mark.parametrize("m", TILE_COLUMNS)
+def test_row_major_column_tiles(routes, m):
+    """One block a tile of the width that test_rv_geometry.py checks."""
+    from tests.test_rv_geometry import rv_max_cols, rv_width
+    status, launches = routes["tiles"][str(m)]
+    assert status == 0 and len(launches) == 1 and launches[0][0].startswith("rv_update_kernel")
+    assert launches[0][1] == -(-m // rv_width(m, rv_max_cols()))

@@ -2,8 +2,10 @@
 itself is covered by the GPU tests):
 
 * tile widths: a matrix of m columns is cut into ceil(m / kRvMaxCols) tiles
-  of equal width rounded up to a multiple of 8 -- every tile fits
-  kRvMaxCols and the tiles cover the columns;
+  of equal width rounded up to a multiple of 64 where that fits kRvMaxCols,
+  else of 8 -- every tile fits kRvMaxCols, the tiles cover the columns and
+  none is empty (that the library launches that many tiles:
+  test_host_routes.py);
 * the lane budget of a block's roles, for every tile width up to
   kRvMaxCols, every alignment of the tile's first unselected slot and
   every number of selected columns in the tile: the whole quads of the
@@ -36,7 +38,8 @@ def rv_max_cols() -> int:
 
 def rv_width(m: int, maxc: int) -> int:
     tiles = max(1, -(-m // maxc))
-    return 8 * -(-max(m, 1) // (8 * tiles))
+    w64 = 64 * -(-max(m, 1) // (64 * tiles))
+    return w64 if w64 <= maxc else 8 * -(-max(m, 1) // (8 * tiles))
 
 
 def test_tile_widths_fit_and_cover():
@@ -47,6 +50,7 @@ def test_tile_widths_fit_and_cover():
         assert w % 8 == 0 and 8 <= w <= maxc, m
         tiles = -(-m // w)
         assert (tiles - 1) * w < m <= tiles * w, m
+        assert tiles <= -(-m // maxc), m
 
 
 def test_role_lane_budget():
