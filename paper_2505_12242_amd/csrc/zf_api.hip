@@ -442,13 +442,17 @@ void set_rv(DevMat& d, int rows, bool allow) {
 }
 
 // Channel-major matrices off the vector path take quads of any alignment from
-// this many rows a channel on, else one element per lane and access.  A short
+// so many rows a channel on, else one element per lane and access: a short
 // channel is one round of loads either way, and the rows after its whole quads
-// a second one: 8 M elements, elements / quads, in us: scores 63 rows 24 / 56,
-// 511 9.5 / 12, 1023 8.9 / 8.5, 4095 12 / 7; later step 159 / 270, 42 / 49, 34 /
-// 34, 36 / 26; hand-over in the third step 163 / 269, 41 / 46, 32 / 31, 35 / 25.
-// (With the statistics, in place, 1023 rows 47 / 52, 1535 44 / 43.)
-constexpr int64_t kCmQuadRows = 1000, kCmQuadStatRows = 1500;
+// a second one.  8 M elements, elements / quads, in us:
+//   scores, packing, Adam    63 rows: scores 24 / 56, later step 159 / 270; 767:
+//                            9.1 / 9.9, 37 / 36, hand-over in the third step 37 /
+//                            36; 895: 8.9 / 9.2, 37 / 34, 37 / 34; 4095: 12 / 7, 36 / 26,
+//                            35 / 25
+//   hand-over of kept ones   (four steps, fixed) 257 rows 82 / 98, 385 71 / 73, 511
+//                            59 / 59, 639 61 / 51; (gated) 385 93 / 82, 639 78 / 58
+//   in place, statistics     1023 rows 47 / 52, 1535 44 / 43
+constexpr int64_t kCmQuadSumRows = 350, kCmQuadRows = 850, kCmQuadStatRows = 1500;
 
 void finish_geometry(DevMat& d, int cn_rows, int up_rows, bool zen = false) {
   set_geometry(d, cn_rows, up_rows);
@@ -473,7 +477,10 @@ void finish_geometry(DevMat& d, int cn_rows, int up_rows, bool zen = false) {
     d.cm_snch = d.n > 0 ? static_cast<int32_t>(ceil_div(d.n, int64_t(zf::kCmSelChunk))) : 0;
     d.cm_unch = d.n > 0 ? static_cast<int32_t>(ceil_div(d.n, zf::kCmUnpackChunk)) : 0;
     d.vec = cm_vec_ok(d) ? 1 : 0;
-    d.cm_quads = d.n >= kCmQuadStatRows ? 2 : d.n >= kCmQuadRows ? 1 : 0;
+    d.cm_quads = d.n >= kCmQuadStatRows  ? zf::kQuadStats
+                 : d.n >= kCmQuadRows    ? zf::kQuadAll
+                 : d.n >= kCmQuadSumRows ? zf::kQuadSums
+                                         : zf::kQuadNone;
     const auto al16 = [](const void* p, int64_t ld) {
       return p != nullptr && aligned(p, 16) && ld % 8 == 0;
     };

@@ -58,6 +58,10 @@ constexpr int kZenCols = 256;
 constexpr int kZenTotalThreads = 256;
 
 enum StateMode : int32_t { kInplace = 0, kRemap = 1, kInit = 2 };
+// Channel-major matrices off the vector path: the passes that move quads of any
+// alignment instead of elements -- none, the hand-over of kept gradients, also
+// the others but for the packing update with the statistics, all.
+enum CmQuads : int32_t { kQuadNone = 0, kQuadSums, kQuadAll, kQuadStats };
 enum Layout : int32_t { kRowMajor = 0, kChannelMajor = 1 };
 
 // One matrix as the kernels see it.  Host-computed geometry is appended.
@@ -117,8 +121,7 @@ struct DevMat {
   int32_t cm_unch;   // channel-major: row chunks per channel (unpack)
   int32_t cm_qpt;    // channel-major: quads (4 elements) per thread in the update (kCmQpt / 2 or kCmQpt)
   int32_t cm_snch;   // channel-major: row chunks per channel of the selected-only Adam grid
-  int32_t cm_quads;  // channel-major, off the vector path: element by element (0), or quads of any
-                     // alignment, but for the packing update with the statistics (1), or there too (2)
+  int32_t cm_quads;  // channel-major, off the vector path: CmQuads
   int32_t scat_vec;  // channel-major: 16-byte path of the weight scatter
   int32_t rv;        // row-major: the 16-byte update kernel can be used (its strides fit)
   int32_t rv_w;      // row-major 16-byte update: tile width (columns)

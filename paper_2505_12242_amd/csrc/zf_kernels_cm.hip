@@ -20,7 +20,7 @@
 // kernels, launched where the table holds one) take the same quads through
 // accesses of 2-byte (bf16) and 4-byte (fp32) alignment, and the up to three
 // rows after a channel's last whole quad element by element; short channels
-// (DevMat::cm_quads unset) all of them.  Measured on a
+// (CmQuads) all of them.  Measured on a
 // 5003 x 3001 weight against one element per lane and access: scores 37.4 -> 8.3
 // us, fused first step 44 -> 27, fused hand-over 44 -> 33.
 #include <type_traits>
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void cm_colnorm_kernel(const DevMat* __re
   const rsrc_t rS = st ? make_rsrc(d.acc1 + j * d.ld_acc1, n * 2) : r;
   // the rows of whole 16-byte groups; RAG: the rest element by element below
   const bool rag = RAG && !d.vec;
-  const int64_t n8 = rag ? (d.cm_quads ? n & ~int64_t(7) : 0) : n;
+  const int64_t n8 = rag ? (d.cm_quads >= kQuadAll ? n & ~int64_t(7) : 0) : n;
   const rsrc_t rO = OUT == 2 ? make_rsrc(d.out + j * d.ld_out, n8 * 4) : r;
   const uint16_t* __restrict__ pg = d.grad + j * d.ld_grad;
   uint16_t* __restrict__ ps = st ? d.acc1 + j * d.ld_acc1 : nullptr;
@@ -472,15 +472,15 @@ __device__ __forceinline__ void cm_pack_piece(int qpt, const Row16& rG, rsrc_t r
 // fn(path, e0, len) over the pieces of rows [e0, e0 + len): the whole of them on
 // the vector path; RAG kernels, off it: the whole quads (of matrices that take
 // them: cm_quads), then the rest.
-// STATS: an update with the statistics.
-template <bool RAG, bool STATS = false, typename Fn>
+// QUADS: the first CmQuads of a matrix that takes quads in this pass.
+template <bool RAG, int QUADS = kQuadAll, typename Fn>
 __device__ __forceinline__ void cm_pieces(const DevMat& d, int64_t e0, int64_t len, Fn fn) {
   if constexpr (!RAG) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
   } else if (d.vec) {
     fn(std::integral_constant<int, kPathVec>{}, e0, len);
   } else {
-    const int64_t n4 = d.cm_quads > (STATS ? 1 : 0) ? len & ~int64_t(3) : 0;
+    const int64_t n4 = d.cm_quads >= QUADS ? len & ~int64_t(3) : 0;
     if (n4 > 0) fn(std::integral_constant<int, kPathRag>{}, e0, n4);
     if (len > n4) fn(std::integral_constant<int, kPathElem>{}, e0 + n4, len - n4);
   }
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
   double ss = 0.0;
 
   if (!sel) {
-    cm_pieces<RAG, STATS && !DEFP>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG, STATS && !DEFP ? kQuadStats : kQuadAll>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       if (mode == kRemap && d.st_P != nullptr) cm_swap_out<P>(d, j, w, e0, len);
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(kThreads) ZF_CM_UPDATE_ATTR void cm_update_kernel(c
       }
     });
   } else if constexpr (ADAM) {
-    cm_pieces<RAG, STATS && !DEFP>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+    cm_pieces<RAG, STATS && !DEFP ? kQuadStats : kQuadAll>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
       constexpr int P = decltype(path)::value;
       const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
       const rsrc_t rP = make_rsrc(d.P + r * d.ld_state + e0, len * 4);
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void cm_handover_deferred_kernel(
   const uint64_t mj = uniform_u64(d.mask[j >> 6]);
   const bool sel = (mj >> (j & 63)) & 1ull;
   double ss = 0.0;
-  cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+  cm_pieces<RAG, kQuadSums>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
     constexpr int P = decltype(path)::value;
     const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);
     const rsrc_t rOut = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
@@ -914,7 +914,7 @@ __device__ __forceinline__ void cm_handover_rows_deferred(const DevMat& d, int32
   const uint64_t mw = uniform_u64(d.mask[j >> 6]);
   const bool sel = (mw >> (j & 63)) & 1ull;
   double ss = 0.0;  // (no statistics)
-  cm_pieces<RAG>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
+  cm_pieces<RAG, kQuadSums>(d, e0, len, [&](auto path, int64_t e0, int64_t len) {
     constexpr int P = decltype(path)::value;
     const rsrc_t rD = make_rsrc(d.out + j * d.ld_out + e0, len * 4);
     const Row16 rG = row16(d.grad + j * d.ld_grad + e0, len);

@@ -199,7 +199,7 @@ def test_row_major_large_sets_in_rows_of_any_alignment(m):
 # without the bf16 stage, the deferred hand-over).
 # Channel-major: channels of n % 8 != 0 through the ragged kernels, n at the
 # edges of a quad, a lane's quads, a chunk and the shortest channels that take
-# quads (1000 rows), next to an aligned matrix and to a long odd one.
+# quads (350 rows in the hand-over of kept gradients, else 850), next to an aligned matrix and to a long odd one.
 def _odd_runner(layout, shapes, how):
     cm = layout == zf.CHANNEL_MAJOR
     R, S, T = 8, 4, 9
@@ -240,15 +240,15 @@ def test_row_major_odd_rows_runner(shape, how):
     _odd_runner(zf.ROW_MAJOR, [shape], how)
 
 
-@pytest.mark.parametrize("n", [1, 3, 5, 255, 999, 1001, 1027, 2047, 2049, 4099])
+@pytest.mark.parametrize("n", [1, 3, 5, 255, 349, 351, 849, 851, 999, 1001, 1027, 2047, 2049, 4099])
 @pytest.mark.parametrize("how", ["stage", "plain", "separate", "deferred"])
 def test_channel_major_odd_channels_runner(n, how):
     _odd_runner(zf.CHANNEL_MAJOR, [(n, 21), (64, 10), (1003, 5)], how)
 
 
-# Channel-major scores of channels of any length: element by element below 1000
+# Channel-major scores of channels of any length: element by element below 850
 # rows, else whole groups of eight and the rows after them, and both stores a refresh may ride on the pass.
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 511, 513, 999, 1001, 2048, 2055, 4099])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 511, 513, 849, 851, 999, 1001, 2048, 2055, 4099])
 def test_channel_major_odd_scores(n):
     m, dev = 13, torch.device("cuda")
     g = gbits(n, m, n)
@@ -277,7 +277,7 @@ def test_channel_major_odd_scores(n):
 # Channel-major hand-over of kept gradients, with four and with eight of them in
 # flight: intervals around both, short and long channels, on and off the aligned
 # path, fixed and gated.  The additions in step order, each one fp32 operation.
-@pytest.mark.parametrize("n", [64, 1023, 4096, 4099])
+@pytest.mark.parametrize("n", [64, 349, 351, 1023, 4096, 4099])
 @pytest.mark.parametrize("steps", [2, 4, 5, 8, 9, 16])
 def test_channel_major_handover_of_kept_gradients(n, steps):
     m, k, dev, hp = 21, 2, torch.device("cuda"), zf.AdamHparams(lr=1e-3)
